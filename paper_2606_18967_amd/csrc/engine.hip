@@ -52,7 +52,7 @@ enum { T_ATTN_D = 0, T_ATTN_V = 1, T_Q4 = 2, T_PROJ = 3, T_LMHEAD = 4, T_SAMPLE 
 
 struct sd_engine_s {
     sd_model_cfg c;
-    int max_slots, max_ctx, max_gamma, rows_max, max_chunks;
+    int max_slots, max_ctx, max_gamma, rows_max;
     int dev;
     bool f32;
     int poison = 0;
@@ -79,6 +79,7 @@ struct sd_engine_s {
     float* gu = nullptr;
     void* act = nullptr;
     float* att_part = nullptr;
+    void* plan = nullptr;        // the running forward's attention plan
     float* samp_part = nullptr;
     float* acc_work = nullptr;
     float2* rope = nullptr;
@@ -234,7 +235,7 @@ static size_t gpart_bytes(const sd_model_cfg& c, int R)
 
 static void free_ws(sd_engine e)
 {
-    void* ps[] = {e->h, e->a, e->qkv, e->qrot, e->att, e->gu, e->act, e->att_part, e->samp_part, e->acc_work, e->rope, e->err,
+    void* ps[] = {e->h, e->a, e->qkv, e->qrot, e->att, e->gu, e->act, e->att_part, e->plan, e->samp_part, e->acc_work, e->rope, e->err,
                   e->pf_lim, e->gpart};
     for (void* p : ps)
         if (p) (void)hipFree(p);
@@ -254,7 +255,6 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     e->max_ctx = max_ctx;
     e->max_gamma = max_gamma;
     e->rows_max = max_slots * (max_gamma + 1);
-    e->max_chunks = (max_ctx + attention_chunk() - 1) / attention_chunk();
     e->f32 = cfg->dtype == SD_DTYPE_F32;
     e->w.assign(sd_num_weights(cfg), nullptr);
     e->qw.assign(4 * cfg->n_layers, nullptr);
@@ -273,7 +273,8 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
         {(void**)&e->att, R * qd * 4},
         {(void**)&e->gu, R * 2 * (size_t)c.ffn * 4},
         {(void**)&e->act, R * c.ffn * 4},
-        {(void**)&e->att_part, attention_part_floats((int)R, c.n_q, c.head_dim, e->max_chunks) * 4},
+        {(void**)&e->att_part, attention_part_floats((int)R, c.n_q, c.n_kv, c.head_dim, e->f32) * 4},
+        {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
         {(void**)&e->samp_part, sample_part_floats((int)R, c.vocab) * 4},
         {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
         {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
@@ -481,9 +482,11 @@ static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const 
     const act_t at = act_of(e, draft);
     const int qkvN = (c.n_q + 2 * c.n_kv) * c.head_dim;
     const int pcls = draft ? T_Q4 : T_PROJ;
+    att_plan plan = attention_plan(B, n, c.n_q, c.n_kv, e->max_ctx, e->f32);
+    attention_plan_bind(plan, e->plan, e->max_slots);
     int S;
     { tscope t(e, T_MISC, s);
-      launch_embed_rmsnorm(r, tokA, sA, tokB, sB, e->w[0], e->f32, c.hidden, c.vocab, e->h, W(e, 0, 0), c.rms_eps, e->a, at, s); }
+      launch_embed_rmsnorm(r, tokA, sA, tokB, sB, e->w[0], e->f32, c.hidden, c.vocab, e->h, W(e, 0, 0), c.rms_eps, e->a, at, plan, s); }
     for (int l = 0; l < c.n_layers; ++l) {
         { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_QKV, e->a, e->qkv, R, qkvN, GEMM_STORE, s); }
         if (!logits && l == c.n_layers - 1) {
@@ -492,11 +495,13 @@ static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const 
             launch_rope_kv(r, e->qkv, e->gpart, S, e->rope, c.n_q, kv, l, e->qrot, s);
             break;
         }
-        attn_split sp;
         { kscope t(e, n == 1 ? T_ATTN_D : T_ATTN_V);      // RoPE and the new K/V rows are part of the attention
-          sp = launch_attention(r, qkv_src{e->qkv, e->gpart, S, e->rope}, e->qrot, c.n_q, kv, l, e->att_part,
-                                e->max_chunks, e->att, at, s, t.start, t.stop); }
-        if (!sp.done) { tscope t(e, T_MISC, s); launch_attention_combine(r, c.n_q, c.head_dim, e->att_part, sp, e->att, at, s); }
+          launch_attention(r, plan, qkv_src{e->qkv, e->gpart, S, e->rope}, e->qrot, c.n_q, kv, l, e->att_part, e->att, at,
+                           s, t.start, t.stop); }
+        if (!plan.whole) {
+            tscope t(e, T_MISC, s);
+            launch_attention_combine(r, plan, c.n_q, c.n_kv, c.head_dim, e->att_part, e->att, at, s);
+        }
         { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_O, e->att, e->h, R, c.hidden, GEMM_ADD, s); }
         { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, W(e, l, 3), e->f32, c.rms_eps, e->a, at, s); }
         bool fused;

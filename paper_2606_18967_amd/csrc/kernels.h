@@ -41,22 +41,41 @@ struct cache_t {
     kv_geom g;
 };
 
+// How one forward's attention divides the cached context among work-groups,
+// made on the device from the sequences' actual lengths by the forward's first
+// kernel (launch_embed_rmsnorm) and read by every layer's attention: items of
+// about equal length, longest first.  An item is a chunk [p0, p1) of one
+// sequence's positions [0, ctx), ctx = basepos + n clipped to max_ctx; nch is
+// the sequence's number of chunks (they are consecutive items), 0 in items past
+// the last.  A sequence without a usable slot or position is one empty item.
+struct att_item { int b, slot, basepos, ctx, p0, p1, nch, nlive; };
+struct att_plan {
+    int2* seq;             // device [B]: first item and number of items of each sequence
+    att_item* item;        // device [max_items]
+    int target, min_chunk; // items wanted (where there are fewer sequences), shortest chunk (a multiple of 32)
+    int max_items;         // grid size: max(target, B), fewer where max_ctx allows no more
+    bool whole;            // every sequence is one item: no combine
+    int mq, zs;            // query tiles per work-group and query-row slices (bf16 cache)
+};
+// the launch geometry of B sequences x n rows (no device pointers)
+att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32);
+size_t attention_plan_bytes(int max_slots, int n_kv);
+void attention_plan_bind(att_plan& p, void* buf, int max_slots);
+
 // ---- model kernels (kernels_model.hip)
 // A kernel input produced by a split-K projection is given as partials P with
 // S > 1 splits ([S][rows][cols], summed on read); S <= 1 means the producer
 // wrote its output directly.
 void launch_embed_rmsnorm(const rows_t& r, const int32_t* tokA, int sA, const int32_t* tokB, int sB,
                           const void* E, int w_f32, int H, int V, float* h, const void* gain, float eps,
-                          void* out, act_t out_t, hipStream_t s);
+                          void* out, act_t out_t, const att_plan& plan, hipStream_t s);
 void launch_add_rmsnorm(float* h, const float* P, int S, int R, int H, const void* gain, int g_f32,
                         float eps, void* out, act_t out_t, hipStream_t s);
 void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, const float2* rope, int n_q,
                     const cache_t& c, int layer, float* q_out, hipStream_t s);
-// Attention in two launches: per-chunk partial softmax-weighted sums into
-// part, then the combine over chunks into out.
-// chunks and chunk length of a split-context attention launch; done when
-// each sequence was a single chunk and the kernel wrote the output itself
-struct attn_split { int chunks, chunk; bool done; };
+// Attention in two launches: each item's softmax-weighted sums (the output
+// itself where a sequence is one item), then the combine over the items of a
+// sequence, which a plan with whole set does without.
 // The QKV projection's output as k_rope_kv reads it (qkv, or S > 1 split-K
 // partials P) with the RoPE table.  The attention applies RoPE and writes the
 // new rows: with a bf16 cache the attention kernel itself rotates its query
@@ -71,13 +90,13 @@ struct qkv_src {
 };
 // ev0/ev1, when given, are bound to the attention kernel's own dispatch
 // (hipExtLaunchKernelGGL): their elapsed time is the kernel's run time.
-attn_split launch_attention(const rows_t& r, qkv_src qs, float* q, int n_q, const cache_t& c, int layer, float* part,
-                            int max_chunks, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0 = nullptr,
-                            hipEvent_t ev1 = nullptr);
-void launch_attention_combine(const rows_t& r, int n_q, int head_dim, const float* part, attn_split sp, void* out,
-                              act_t out_t, hipStream_t s);
-size_t attention_part_floats(int R, int n_q, int head_dim, int max_chunks);
-int attention_chunk();
+void launch_attention(const rows_t& r, const att_plan& plan, qkv_src qs, float* q, int n_q, const cache_t& c, int layer,
+                      float* part, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0 = nullptr,
+                      hipEvent_t ev1 = nullptr);
+void launch_attention_combine(const rows_t& r, const att_plan& plan, int n_q, int n_kv, int head_dim, const float* part,
+                              void* out, act_t out_t, hipStream_t s);
+// partial-result floats for any forward of up to R rows
+size_t attention_part_floats(int R, int n_q, int n_kv, int head_dim, int kv_f32);
 void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, hipStream_t s);
 void launch_kv_advance(int B, const int32_t* slots, const int32_t* inc, int inc_const,
                        int32_t* kv_len, int max_slots, uint32_t* err, hipStream_t s);

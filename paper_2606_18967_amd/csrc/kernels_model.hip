@@ -63,13 +63,121 @@ template <> __device__ __forceinline__ float4 load4<uint16_t>(const uint16_t* p)
                        __uint_as_float(v.y & 0xffff0000u));
 }
 
-// h[row] = E[token(row)];  out[row] = RMSNorm(h[row]) * gain
+// The attention plan of a forward (att_plan, kernels.h), by one work-group.
+// With no more sequences than the target, the chunk length is the shortest of
+// 64 candidates, from total / target up to the longest context, that makes at
+// most `target` chunks: every item is then resident at once, and they are of
+// about equal length whatever the contexts are.  (Chunks cut by max_ctx instead
+// left 13 ragged sequences in a cache with room for 8192 positions 200
+// work-groups: 53 us per launch.)  More sequences than the target stay whole.
+// Items go longest first, so that the last ones to start are short.  Before and
+// after, 8B shape: 53.3 -> 34.7 us (13 sequences of 1500-4500), 22.1 -> 16.9 (4),
+// 14.6 -> 11.0 (one of 2048), verify of 16 x 8 rows 80.8 -> 60.4; in order of
+// length, 200 sequences of 512-1536: 181 -> 161.
+#ifndef ATT_FULL_CHUNK
+#define ATT_FULL_CHUNK 512
+#endif
+constexpr int PLAN_UNIT = 32;       // chunk lengths are multiples of a wave's block
+constexpr int PLAN_SEQS = 512;      // sequences planned in LDS (more, always whole, keep their order)
+
+__device__ void make_att_plan(const rows_t& r, const att_plan& pl)
+{
+    __shared__ att_item s_it[PLAN_SEQS];
+    __shared__ int s_len[PLAN_SEQS], s_first[PLAN_SEQS];
+    __shared__ int s_cnt[64], s_sum, s_top, s_items;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    auto seq_of = [&](int b) {
+        att_item it = {b, r.slots[b], 0, 0, 0, 0, 1, 0};
+        it.nlive = r.lim ? min(r.n, max(r.lim[b], 0)) : r.n;
+        if (it.slot >= 0 && it.slot < r.max_slots) {
+            it.basepos = r.kv_len[it.slot] + r.off;
+            it.ctx = max(0, min(it.basepos + r.n, r.max_ctx));
+        }
+        return it;
+    };
+    if (r.B > PLAN_SEQS) {
+        for (int b = tid; b < r.B; b += nt) {
+            att_item it = seq_of(b);
+            it.p1 = it.ctx;
+            pl.item[b] = it;
+            pl.seq[b] = make_int2(b, 1);
+        }
+        return;
+    }
+    if (tid < 64) s_cnt[tid] = 0;
+    if (tid == 64) s_sum = s_top = s_items = 0;
+    __syncthreads();
+    for (int b = tid; b < r.B; b += nt) {
+        const att_item it = seq_of(b);
+        s_it[b] = it;
+        s_first[b] = 0;
+        atomicAdd(&s_sum, it.ctx);
+        atomicMax(&s_top, it.ctx);
+    }
+    __syncthreads();
+    int ch = max((s_top + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, pl.min_chunk);
+    if (r.B < pl.max_items) {
+        // candidate k: between the even share and the longest context, denser near the share
+        // (with little context in all, a quarter of the target's work-groups: shorter chunks would be all prologue)
+        const int few = max(pl.target / 4, 1);
+        const int even = (s_sum + pl.target - 1) / pl.target, fewer = (s_sum + few - 1) / few;
+        const int share = max(max(even, min(fewer, ATT_FULL_CHUNK)), pl.min_chunk);
+        const int base = min((share + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, ch);
+        const int more = (ch - base) / PLAN_UNIT;
+        auto cand = [&](int k) { return base + (more * (k * k) + 63 * 63 - 1) / (63 * 63) * PLAN_UNIT; };
+        const int k = tid & 63, ck = cand(k);
+        int cnt = 0;
+        for (int b = tid >> 6; b < r.B; b += nt >> 6) cnt += max(1, (s_it[b].ctx + ck - 1) / ck);
+        atomicAdd(&s_cnt[k], cnt);
+        __syncthreads();
+        const uint64_t fits = __builtin_amdgcn_ballot_w64(s_cnt[k] <= min(pl.target, pl.max_items));
+        ch = cand(fits ? (int)__builtin_ctzll(fits) : 63);
+    }
+    for (int b = tid; b < r.B; b += nt) {
+        const int ctx = s_it[b].ctx, nch = max(1, (ctx + ch - 1) / ch);
+        s_it[b].nch = nch;
+        s_len[b] = ((ctx + nch - 1) / nch + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT;   // <= ch: no chunk is empty
+        atomicAdd(&s_items, nch);
+    }
+    __syncthreads();
+    // a sequence's first item: the items of all sequences with longer chunks (ties: the lower index first)
+    const int parts = max(nt / r.B, 1);
+    for (int t = tid; t < r.B * parts; t += nt) {
+        const int b = t / parts, len = s_len[b];
+        int first = 0;
+        for (int o = t - b * parts; o < r.B; o += parts) {
+            const int lo = s_len[o];
+            first += lo > len || (lo == len && o < b) ? s_it[o].nch : 0;
+        }
+        atomicAdd(&s_first[b], first);
+    }
+    __syncthreads();
+    for (int b = tid; b < r.B; b += nt) {
+        att_item it = s_it[b];
+        const int first = s_first[b], len = s_len[b], nch = it.nch;
+        pl.seq[b] = make_int2(first, nch);
+        for (int c = 0; c < nch && first + c < pl.max_items; ++c) {
+            it.p0 = c * len;
+            it.p1 = min(it.p0 + len, it.ctx);
+            pl.item[first + c] = it;
+        }
+    }
+    const att_item none = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = s_items + tid; i < pl.max_items; i += nt) pl.item[i] = none;
+}
+
+// h[row] = E[token(row)];  out[row] = RMSNorm(h[row]) * gain.  One more
+// work-group than rows makes the forward's attention plan.
 template <typename T, typename O>
 __global__ void __launch_bounds__(1024) k_embed_rmsnorm(rows_t r, const int32_t* tokA, int sA, const int32_t* tokB,
                                                         int sB, const T* E, int H, int V, float* h, const T* gain,
-                                                        float eps, void* out)
+                                                        float eps, void* out, att_plan plan)
 {
     __shared__ float red[16];
+    if (blockIdx.x == gridDim.x - 1) {
+        make_att_plan(r, plan);
+        return;
+    }
     const int row = blockIdx.x;
     const int b = row / r.n, i = row - b * r.n;
     const bool pad = r.lim && i >= r.lim[b];            // a padding row: embedded as token 0, never cached
@@ -234,18 +342,24 @@ __global__ void __launch_bounds__(256) k_rope_kv(rows_t r, const float* qkv, con
 
 // ------------------------------------------------------------------ attention
 // Split-context decode attention (flash-decoding style), fp32 arithmetic.
-// Work-group (b, kv head, chunk c) covers context positions [c*CH, (c+1)*CH)
-// of that sequence; query row (i, head h) of the sequence attends positions
-// [0, kv_len + off + i] (causal inside the block of new tokens).  Each
-// work-group writes (m, l, o[d]) per query row and head; k_attn_combine
-// merges the chunks.  D/8 lanes share one position, 8 dims per lane.
-constexpr int ATT_CH = 256;
-constexpr int ATT_RG = 4;   // query rows per pass
+// Work-group (item, kv head) covers the item's positions [p0, p1); query row
+// (i, head h) of the sequence attends positions [0, basepos + i] (causal inside
+// the block of new tokens).  Each work-group writes (m, l, o[d]) per query row
+// and head for k_attn_combine, or the output itself where the sequence is one
+// item.  D/8 lanes share one position, 8 dims per lane.
+constexpr int ATT_CH = 256;   // shortest chunk
+constexpr int ATT_RG = 4;     // query rows per pass
+
+// partial result (m, l, o[d]) of query row qrow (of QR per KV head) of an item
+__device__ __forceinline__ size_t part_index(int item, int n_kv, int kvh, int QR, int qrow, int D)
+{
+    return (((size_t)item * n_kv + kvh) * QR + qrow) * (D + 2);
+}
 
 template <typename T, int D>
 __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, int n_q, int n_kv,
                                                       const T* kc, const T* vc, kv_geom kg, int layer, float* part,
-                                                      int max_chunks)
+                                                      att_plan plan, float* out)
 {
     constexpr int LPP = D / 8;          // lanes per position
     constexpr int PPW = WAVE / LPP;     // positions per wave-step
@@ -254,16 +368,10 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
     __shared__ float s_l[NPG][ATT_RG];
     __shared__ float s_o[NPG][ATT_RG][D];
 
-    int b = blockIdx.x / n_kv, kvh = blockIdx.x - b * n_kv;
-    int c = blockIdx.y;
-    int slot = r.slots[b];
-    if (slot < 0 || slot >= r.max_slots) return;   // flagged by k_rope_kv
-    int basepos = r.kv_len[slot] + r.off;
-    int ctx = basepos + r.n;
-    if (ctx > r.max_ctx) ctx = r.max_ctx;
-    int p0 = c * ATT_CH;
-    if (p0 >= ctx) return;
-    int p1 = min(p0 + ATT_CH, ctx);
+    const int item = blockIdx.y, kvh = blockIdx.x;
+    const att_item it = plan.item[item];
+    if (it.nch == 0) return;
+    const int b = it.b, slot = it.slot, basepos = it.basepos, p0 = it.p0, p1 = it.p1;   // p0 == p1: flagged by k_rope_kv
 
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int pg = lane / LPP;                 // position group within the wave
@@ -350,7 +458,11 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
             }
             int g = qr / r.n, i = qr - g * r.n;
             int hq = kvh * G + g;
-            float* pp = part + (((size_t)(b * r.n + i) * n_q + hq) * max_chunks + c) * (D + 2);
+            if (it.nch == 1) {
+                out[((size_t)(b * r.n + i) * n_q + hq) * D + k] = ls > 0.f ? os / ls : 0.f;
+                continue;
+            }
+            float* pp = part + part_index(item, n_kv, kvh, QR, qr, D);
             if (k == 0) { pp[0] = mm; pp[1] = ls; }
             pp[2 + k] = os;
         }
@@ -358,10 +470,9 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
     }
 }
 
-// MFMA attention for a bf16 cache.  Work-group (b, kv head, chunk, query-row
-// slice z): a sequence's context is split evenly into ceil(ctx / ch) chunks
-// and each wave takes a quarter of its chunk in blocks of 32 positions.  Per
-// block:
+// MFMA attention for a bf16 cache.  Work-group (item, kv head, query-row
+// slice z) covers the item's positions [p0, p1); its four waves take them in
+// blocks of 32 positions in turn.  Per block:
 //   S^T = K Q^T with v_mfma_f32_16x16x32_bf16: K rows straight from global
 //   memory (lane l: position l%16 of a 16-row tile, dims 8*(4ks + l/16)+0..7),
 //   Q^T pre-scaled by log2(e)/sqrt(d).  Lane l then holds the scores of query
@@ -377,10 +488,9 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 // than 8, bounding the exp2 terms by 256); the four waves are merged
 // through LDS and the chunk result (m in natural-log units, l, o[d]) goes to
 // the same partial buffer k_attn_combine reads.
-// Chunk length of the MFMA kernel, chosen per launch: enough chunks per
-// sequence for about ATT_TARGET_WGS work-groups in all (two per CU), each at
-// least ATT_MIN_CHUNK positions, so a large batch streams a whole context per
-// work-group and a small one still fills the GPU.
+// About ATT_TARGET_WGS work-groups are wanted in all (two per CU), each of at
+// least ATT_MIN_CHUNK positions, so a large batch streams whole contexts and a
+// small one still fills the GPU.
 #ifndef ATT_INTERLEAVE
 #define ATT_INTERLEAVE 1
 #endif
@@ -394,7 +504,7 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 #define ATT_TARGET_WGS 512
 #endif
 #ifndef ATT_MIN_CHUNK
-#define ATT_MIN_CHUNK 512
+#define ATT_MIN_CHUNK 128
 #endif
 
 // two waves per SIMD where the registers allow it without spills (one query
@@ -410,7 +520,7 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 // slot, position and page flags for them.
 template <int D, int MQ, bool PAGED>
 __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, int n_q, int n_kv, const uint16_t* kc,
-                                                   const uint16_t* vc, kv_geom kg, int layer, float* part, int max_chunks, int ch,
+                                                   const uint16_t* vc, kv_geom kg, int layer, float* part, att_plan plan,
                                                    void* out, int out_t, qkv_src qs)
 {
     constexpr int KS = D / 32;      // k-steps over the head dim
@@ -420,15 +530,23 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     __shared__ __attribute__((aligned(16))) uint16_t Vs[4][32 * LDV];
     __shared__ float s_ml[4][2][16];
 
-    const int b = blockIdx.x / n_kv, kvh = blockIdx.x - b * n_kv;
-    const int c = blockIdx.y, z = blockIdx.z;
-    // wave-uniform by construction; readfirstlane lets the compiler keep them
-    // (and the buffer resources built from them) in scalar registers
-    const int slot = __builtin_amdgcn_readfirstlane(r.slots[b]);
-    if (slot < 0 || slot >= r.max_slots) {         // flagged once per sequence; a direct output is zeroed
-        if (c == 0 && z == 0 && kvh == 0 && threadIdx.x == 0) flag_error(r.err, ERR_SLOT);
+    const int item = blockIdx.y, kvh = blockIdx.x, z = blockIdx.z;
+    // wave-uniform by construction; readfirstlane lets the compiler keep the
+    // fields (and the buffer resources built from them) in scalar registers
+    const att_item it = plan.item[item];
+    if (it.nch == 0) return;
+    const int b = __builtin_amdgcn_readfirstlane(it.b), slot = __builtin_amdgcn_readfirstlane(it.slot);
+    const int basepos = __builtin_amdgcn_readfirstlane(it.basepos), ctx = __builtin_amdgcn_readfirstlane(it.ctx);
+    const int p0 = __builtin_amdgcn_readfirstlane(it.p0), p1 = __builtin_amdgcn_readfirstlane(it.p1);
+    const int nlive = __builtin_amdgcn_readfirstlane(it.nlive);   // rows (b, i >= nlive) are padding: neither cached nor flagged
+    // a live row's slot, or its position outside [0, max_ctx), is flagged once per sequence
+    if (p0 == 0 && z == 0 && kvh == 0 && threadIdx.x == 0) {
+        if (slot < 0 || slot >= r.max_slots) flag_error(r.err, ERR_SLOT);
+        else if (nlive > 0 && (basepos < 0 || basepos + nlive > r.max_ctx)) flag_error(r.err, ERR_CTX);
+    }
+    if (p0 >= p1) {                                // no usable slot or position: the output is zeros
         const int G = n_q / n_kv;
-        for (int idx = threadIdx.x; out && idx < 16 * MQ * D; idx += 256) {
+        for (int idx = threadIdx.x; idx < 16 * MQ * D; idx += 256) {
             const int qrow = z * 16 * MQ + idx / D, d = idx % D;
             if (qrow >= G * r.n) continue;
             const int g = qrow / r.n, i = qrow - g * r.n;
@@ -439,21 +557,6 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
         }
         return;
     }
-    const int basepos = __builtin_amdgcn_readfirstlane(r.kv_len[slot]) + r.off;
-    int ctx = basepos + r.n;
-    if (ctx > r.max_ctx) ctx = r.max_ctx;
-    // rows (b, i >= nlive) are padding: neither cached nor flagged
-    const int nlive = r.lim ? min(r.n, max(__builtin_amdgcn_readfirstlane(r.lim[b]), 0)) : r.n;
-    if (c == 0 && z == 0 && kvh == 0 && threadIdx.x == 0 && nlive > 0 &&
-        (basepos < 0 || basepos + nlive > r.max_ctx))
-        flag_error(r.err, ERR_CTX);                 // a live row's position outside [0, max_ctx)
-    // the sequence's ceil(ctx / ch) chunks (the count k_attn_combine reads)
-    // split its context evenly, in multiples of 32 positions
-    const int nch = (ctx + ch - 1) / ch;
-    const int clen = ((ctx + nch - 1) / nch + 31) & ~31;
-    const int p0 = c * clen;
-    if (p0 >= ctx) return;
-    const int p1 = min(p0 + clen, ctx);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int cq = lane >> 4, lr = lane & 15;
     const int G = n_q / n_kv, QR = G * r.n;
@@ -488,7 +591,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     // work-group reads K and V as two contiguous streams
     const int wq0 = p0 + 32 * w, wq1 = p1, wstep = 128;
 #else
-    const int wlen = ((clen + 3) / 4 + 31) & ~31;                  // positions per wave
+    const int wlen = ((p1 - p0 + 3) / 4 + 31) & ~31;               // positions per wave
     const int wq0 = p0 + w * wlen, wq1 = min(wq0 + wlen, p1), wstep = 32;
 #endif
     // K fragments of the two 16-position tiles and the V block of the block at
@@ -572,6 +675,9 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     // set requests the next block's K and V there
     auto block = [&](int blk, const u32x4 (&kf)[2][KS], const u32x4 (&vv)[CPP / 2], auto after_k, auto after_v) {
         bf16x8 pf[MQ];
+        // a block before the new rows that ends in the wave's range is visible to every row as a whole: no
+        // comparisons there, and exp2 without the scaling for denormal results (32B verify 341.8 -> 338.1 us)
+        const bool masked = blk + 32 > wq1 || blk + 31 > basepos;
 #pragma unroll
         for (int mt = 0; mt < MQ; ++mt) {
             floatx4 st[2];
@@ -584,17 +690,17 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                                                                      st[pt], 0, 0, 0);
             }
             if (mt == MQ - 1) after_k();
-            float bm = -INFINITY;
+            if (masked) {
 #pragma unroll
-            for (int pt = 0; pt < 2; ++pt)
+                for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int pos = blk + 16 * pt + 4 * cq + i;
-                    float sv = st[pt][i];
-                    if (pos >= wq1 || pos > lim[mt]) sv = -INFINITY;
-                    st[pt][i] = sv;
-                    bm = fmaxf(bm, sv);
-                }
+                    for (int i = 0; i < 4; ++i) {
+                        const int pos = blk + 16 * pt + 4 * cq + i;
+                        if (pos >= wq1 || pos > lim[mt]) st[pt][i] = -INFINITY;
+                    }
+            }
+            float bm = fmaxf(fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3])),
+                             fmaxf(fmaxf(st[1][0], st[1][1]), fmaxf(st[1][2], st[1][3])));
             bm = fmaxf(bm, __shfl_xor(bm, 16, WAVE));
             bm = fmaxf(bm, __shfl_xor(bm, 32, WAVE));
             // lazy rescaling: a row moves its reference max (and rescales its
@@ -603,7 +709,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
             const bool need = bm > m[mt] + 8.f;
             if (__builtin_amdgcn_ballot_w64(need)) {
                 const float mn = need ? bm : m[mt];
-                const float corr = m[mt] == -INFINITY ? 0.f : exp2f(m[mt] - mn);
+                const float corr = m[mt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[mt] - mn);
                 m[mt] = mn;
                 lsum[mt] *= corr;
 #pragma unroll
@@ -611,14 +717,14 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
 #pragma unroll
                     for (int i = 0; i < 4; ++i) o[mt][nb][i] *= corr;
             }
-            const float mn = m[mt];
+            // a row without a visible position so far (m = -inf) subtracts 0: exp2(-inf) = 0
+            const float mn = m[mt] == -INFINITY ? 0.f : m[mt];
             float pv[8];
 #pragma unroll
             for (int pt = 0; pt < 2; ++pt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float x = st[pt][i];
-                    pv[pt * 4 + i] = x == -INFINITY ? 0.f : exp2f(x - mn);
+                    pv[pt * 4 + i] = __builtin_amdgcn_exp2f(st[pt][i] - mn);
                     lsum[mt] += pv[pt * 4 + i];
                 }
             pf[mt] = __builtin_bit_cast(bf16x8, (u32x4){pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]),
@@ -815,8 +921,8 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                 }
             }
             const int g = qrow / r.n, i = qrow - g * r.n;
-            if (out) {
-                // a single chunk per sequence: the normalized output directly (what
+            if (it.nch == 1) {
+                // the sequence's only item: the normalized output directly (what
                 // k_attn_combine computes from one chunk)
                 const size_t oi = ((size_t)(b * r.n + i) * n_q + kvh * G + g) * D + d;
                 const float v = ls > 0.f ? os / ls : 0.f;
@@ -825,7 +931,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                 else store_act<float>(out, oi, v);
                 continue;
             }
-            float* pp = part + (((size_t)(b * r.n + i) * n_q + kvh * G + g) * max_chunks + c) * (D + 2);
+            float* pp = part + part_index(item, n_kv, kvh, QR, qrow, D);
             if (d == 0) { pp[0] = mm * LN2; pp[1] = ls; }
             pp[2 + d] = os;
         }
@@ -833,16 +939,16 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
 }
 
 template <typename O>
-__global__ void k_attn_combine(rows_t r, int n_q, int D, const float* part, int max_chunks, int chunk, void* out)
+__global__ void k_attn_combine(rows_t r, att_plan plan, int n_q, int n_kv, int D, const float* part, void* out)
 {
-    int row = blockIdx.x / n_q, hq = blockIdx.x - row * n_q;
-    int b = row / r.n;
-    int slot = r.slots[b];
-    int ctx = 0;
-    if (slot >= 0 && slot < r.max_slots) ctx = min(r.kv_len[slot] + r.off + r.n, r.max_ctx);
-    int nch = (ctx + chunk - 1) / chunk;
-    if (nch > max_chunks) nch = max_chunks;
-    const float* pp = part + ((size_t)row * n_q + hq) * max_chunks * (D + 2);
+    const int row = blockIdx.x / n_q, hq = blockIdx.x - row * n_q;
+    const int b = row / r.n, i = row - b * r.n;
+    const int2 sq = plan.seq[b];
+    const int nch = sq.y;
+    if (nch <= 1) return;                               // the attention wrote the output
+    const int G = n_q / n_kv, QR = G * r.n, kvh = hq / G;
+    const float* pp = part + part_index(sq.x, n_kv, kvh, QR, (hq - kvh * G) * r.n + i, D);
+    const size_t cs = (size_t)n_kv * QR * (D + 2);      // to the next chunk
     // chunks are merged in order, sixteen at a time: the loads of a batch go
     // out together (past the last chunk they repeat chunk nch - 1 and are not
     // used), and a later batch with a larger maximum rescales the sums so far.
@@ -855,7 +961,7 @@ __global__ void k_attn_combine(rows_t r, int n_q, int D, const float* part, int 
             float cm[CB], cl[CB], co[CB];
 #pragma unroll
             for (int u = 0; u < CB; ++u) {
-                const float* pc = pp + (size_t)min(c0 + u, nch - 1) * (D + 2);
+                const float* pc = pp + min(c0 + u, nch - 1) * cs;
                 cm[u] = pc[0];
                 cl[u] = pc[1];
                 co[u] = pc[2 + k];
@@ -960,21 +1066,21 @@ __global__ void k_kv_poison(const int32_t* slots, const int32_t* kv_len, int spa
 // ======================================================================= launchers
 template <typename T>
 static void embed_norm_t(const rows_t& r, const int32_t* tokA, int sA, const int32_t* tokB, int sB, const T* E, int H,
-                         int V, float* h, const T* gain, float eps, void* out, act_t t, hipStream_t s)
+                         int V, float* h, const T* gain, float eps, void* out, act_t t, const att_plan& pl, hipStream_t s)
 {
-    const int R = r.B * r.n;
+    const int g = r.B * r.n + 1;                              // rows, then the attention plan
     const int th = H >= 4096 ? 1024 : 256;
-    if (t == ACT_F32) k_embed_rmsnorm<T, float><<<R, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out);
-    else if (t == ACT_BF16) k_embed_rmsnorm<T, uint16_t><<<R, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out);
-    else k_embed_rmsnorm<T, _Float16><<<R, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out);
+    if (t == ACT_F32) k_embed_rmsnorm<T, float><<<g, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out, pl);
+    else if (t == ACT_BF16) k_embed_rmsnorm<T, uint16_t><<<g, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out, pl);
+    else k_embed_rmsnorm<T, _Float16><<<g, th, 0, s>>>(r, tokA, sA, tokB, sB, E, H, V, h, gain, eps, out, pl);
 }
 
 void launch_embed_rmsnorm(const rows_t& r, const int32_t* tokA, int sA, const int32_t* tokB, int sB, const void* E,
                           int w_f32, int H, int V, float* h, const void* gain, float eps, void* out, act_t out_t,
-                          hipStream_t s)
+                          const att_plan& plan, hipStream_t s)
 {
-    if (w_f32) embed_norm_t(r, tokA, sA, tokB, sB, (const float*)E, H, V, h, (const float*)gain, eps, out, out_t, s);
-    else embed_norm_t(r, tokA, sA, tokB, sB, (const uint16_t*)E, H, V, h, (const uint16_t*)gain, eps, out, out_t, s);
+    if (w_f32) embed_norm_t(r, tokA, sA, tokB, sB, (const float*)E, H, V, h, (const float*)gain, eps, out, out_t, plan, s);
+    else embed_norm_t(r, tokA, sA, tokB, sB, (const uint16_t*)E, H, V, h, (const uint16_t*)gain, eps, out, out_t, plan, s);
 }
 
 template <typename G, int NPT>
@@ -1020,11 +1126,46 @@ void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, co
                                                  (uint16_t*)c.v, c.g, layer, q_out, upw);
 }
 
-int attention_chunk() { return ATT_CH < ATT_MIN_CHUNK ? ATT_CH : ATT_MIN_CHUNK; }
-
-size_t attention_part_floats(int R, int n_q, int head_dim, int max_chunks)
+att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32)
 {
-    return (size_t)R * n_q * max_chunks * (head_dim + 2);
+    att_plan p = {};
+    const int QR = n_q / n_kv * n;
+    p.mq = QR > 48 ? 4 : (QR + 15) / 16;
+    p.zs = kv_f32 ? 1 : (QR + 16 * p.mq - 1) / (16 * p.mq);
+    p.min_chunk = kv_f32 ? ATT_CH : ATT_MIN_CHUNK;
+    p.target = ATT_TARGET_WGS / (n_kv * p.zs);
+    if (p.target < 1) p.target = 1;
+    const long long cap = (long long)B * ((max_ctx + p.min_chunk - 1) / p.min_chunk);   // chunks the cache has room for
+    p.max_items = B >= p.target ? B : (cap < p.target ? (int)cap : p.target);
+    p.whole = p.max_items == B;
+    return p;
+}
+
+// seq [max_slots], item [max(max_slots, ATT_TARGET_WGS / n_kv)]
+static size_t plan_seq_bytes(int max_slots) { return ((size_t)max_slots * sizeof(int2) + 63) & ~(size_t)63; }
+
+size_t attention_plan_bytes(int max_slots, int n_kv)
+{
+    const size_t t = ATT_TARGET_WGS / n_kv > max_slots ? ATT_TARGET_WGS / n_kv : max_slots;
+    return plan_seq_bytes(max_slots) + t * sizeof(att_item);
+}
+
+void attention_plan_bind(att_plan& p, void* buf, int max_slots)
+{
+    p.seq = (int2*)buf;
+    p.item = (att_item*)((char*)buf + plan_seq_bytes(max_slots));
+}
+
+// only items of a sequence cut in several are stored, and then there are at most `target` of them
+size_t attention_part_floats(int R, int n_q, int n_kv, int head_dim, int kv_f32)
+{
+    size_t most = 0;
+    for (int n = 1; n <= R; ++n) {
+        const att_plan p = attention_plan(1, n, n_q, n_kv, 1 << 30, kv_f32);
+        const size_t f = p.whole ? 0 : (size_t)p.target * n * n_q * (head_dim + 2);
+        most = f > most ? f : most;
+    }
+    return most > 64 ? most : 64;
 }
 
 // a launch whose events (if any) are bound to the kernel's dispatch
@@ -1036,16 +1177,14 @@ static void launch_ev(F kern, dim3 grid, dim3 block, hipStream_t s, hipEvent_t e
 }
 
 template <int D, bool PAGED>
-static void attn_mfma_launch(int MQ, dim3 grid, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, const rows_t& r,
-                             int n_q, const cache_t& c, int layer, float* part, int mch, int ch, void* out, int out_t,
-                             qkv_src qs)
+static void attn_mfma_launch(const rows_t& r, const att_plan& pl, qkv_src qs, int n_q, const cache_t& c, int layer,
+                             float* part, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const uint16_t* kc = (const uint16_t*)c.k;
-    const uint16_t* vc = (const uint16_t*)c.v;
     auto go = [&](auto kern) {
-        launch_ev(kern, grid, dim3(256), s, ev0, ev1, r, n_q, c.n_kv, kc, vc, c.g, layer, part, mch, ch, out, out_t, qs);
+        launch_ev(kern, dim3(c.n_kv, pl.max_items, pl.zs), dim3(256), s, ev0, ev1, r, n_q, c.n_kv, (const uint16_t*)c.k,
+                  (const uint16_t*)c.v, c.g, layer, part, pl, out, (int)out_t, qs);
     };
-    switch (MQ) {
+    switch (pl.mq) {
         case 1: go(k_attn_mfma<D, 1, PAGED>); break;
         case 2: go(k_attn_mfma<D, 2, PAGED>); break;
         case 3: go(k_attn_mfma<D, 3, PAGED>); break;
@@ -1053,60 +1192,36 @@ static void attn_mfma_launch(int MQ, dim3 grid, hipStream_t s, hipEvent_t ev0, h
     }
 }
 
-template <typename T, int D>
-static attn_split attn_t(const rows_t& r, const float* q, int n_q, const cache_t& c, int layer, float* part,
-                         int max_chunks, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
-                         qkv_src qs)
+template <int D>
+static void attn_d(const rows_t& r, const att_plan& pl, qkv_src qs, float* q, int n_q, const cache_t& c, int layer,
+                   float* part, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    if constexpr (sizeof(T) == 2) {
-        // bf16 cache: MFMA kernel.  max_chunks (the partial buffer's chunk
-        // capacity) counts chunks of attention_chunk() <= ATT_MIN_CHUNK positions.
-        const int QR = (n_q / c.n_kv) * r.n;
-        const int MQ = QR > 48 ? 4 : (QR + 15) / 16;
-        const int zs = (QR + 16 * MQ - 1) / (16 * MQ);
-        const int per_chunk = r.B * c.n_kv * zs;                       // work-groups per chunk index
-        const int want = (ATT_TARGET_WGS + per_chunk - 1) / per_chunk;   // chunks per sequence at capacity
-        int ch = (r.max_ctx + want - 1) / want;
-        ch = ((ch > ATT_MIN_CHUNK ? ch : ATT_MIN_CHUNK) + 31) & ~31;
-        int mch = (r.max_ctx + ch - 1) / ch;
-        if (mch > max_chunks) {                                          // cannot happen for ch >= attention_chunk()
-            mch = max_chunks;
-            ch = ((r.max_ctx + mch - 1) / mch + 31) & ~31;
-        }
-        dim3 grid(r.B * c.n_kv, mch, zs);
-        // one chunk per sequence: the kernel writes the final output itself
-        void* o = mch == 1 ? out : nullptr;
-        if (c.g.bt) attn_mfma_launch<D, true>(MQ, grid, s, ev0, ev1, r, n_q, c, layer, part, mch, ch, o, out_t, qs);
-        else attn_mfma_launch<D, false>(MQ, grid, s, ev0, ev1, r, n_q, c, layer, part, mch, ch, o, out_t, qs);
-        return attn_split{mch, ch, o != nullptr};
+    if (c.kv_f32) {
+        // the fp32 kernel reads rotated queries: k_rope_kv writes them (and the new K/V rows) first
+        launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, q, s);
+        launch_ev(k_attn_partial<float, D>, dim3(c.n_kv, pl.max_items), dim3(256), s, ev0, ev1, r, (const float*)q, n_q,
+                  c.n_kv, (const float*)c.k, (const float*)c.v, c.g, layer, part, pl, (float*)out);
+    } else if (c.g.bt) {
+        attn_mfma_launch<D, true>(r, pl, qs, n_q, c, layer, part, out, out_t, s, ev0, ev1);
     } else {
-        dim3 grid(r.B * c.n_kv, max_chunks);
-        launch_ev(k_attn_partial<T, D>, grid, dim3(256), s, ev0, ev1, r, q, n_q, c.n_kv, (const T*)c.k, (const T*)c.v,
-                  c.g, layer, part, max_chunks);
-        return attn_split{max_chunks, ATT_CH, false};
+        attn_mfma_launch<D, false>(r, pl, qs, n_q, c, layer, part, out, out_t, s, ev0, ev1);
     }
 }
 
-attn_split launch_attention(const rows_t& r, qkv_src qs, float* q, int n_q, const cache_t& c, int layer, float* part,
-                            int max_chunks, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
+void launch_attention(const rows_t& r, const att_plan& plan, qkv_src qs, float* q, int n_q, const cache_t& c, int layer,
+                      float* part, void* out, act_t out_t, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    // the fp32 cache's kernel reads rotated queries: k_rope_kv writes them (and the new K/V rows) first
-    if (c.kv_f32) launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, q, s);
-    if (c.head_dim == 128) {
-        if (c.kv_f32) return attn_t<float, 128>(r, q, n_q, c, layer, part, max_chunks, out, out_t, s, ev0, ev1, qs);
-        return attn_t<uint16_t, 128>(r, q, n_q, c, layer, part, max_chunks, out, out_t, s, ev0, ev1, qs);
-    }
-    if (c.kv_f32) return attn_t<float, 64>(r, q, n_q, c, layer, part, max_chunks, out, out_t, s, ev0, ev1, qs);
-    return attn_t<uint16_t, 64>(r, q, n_q, c, layer, part, max_chunks, out, out_t, s, ev0, ev1, qs);
+    if (c.head_dim == 128) attn_d<128>(r, plan, qs, q, n_q, c, layer, part, out, out_t, s, ev0, ev1);
+    else attn_d<64>(r, plan, qs, q, n_q, c, layer, part, out, out_t, s, ev0, ev1);
 }
 
-void launch_attention_combine(const rows_t& r, int n_q, int head_dim, const float* part, attn_split sp, void* out,
-                              act_t out_t, hipStream_t s)
+void launch_attention_combine(const rows_t& r, const att_plan& plan, int n_q, int n_kv, int head_dim, const float* part,
+                              void* out, act_t out_t, hipStream_t s)
 {
     const int R = r.B * r.n, D = head_dim;
-    if (out_t == ACT_F32) k_attn_combine<float><<<R * n_q, D, 0, s>>>(r, n_q, D, part, sp.chunks, sp.chunk, out);
-    else if (out_t == ACT_BF16) k_attn_combine<uint16_t><<<R * n_q, D, 0, s>>>(r, n_q, D, part, sp.chunks, sp.chunk, out);
-    else k_attn_combine<_Float16><<<R * n_q, D, 0, s>>>(r, n_q, D, part, sp.chunks, sp.chunk, out);
+    if (out_t == ACT_F32) k_attn_combine<float><<<R * n_q, D, 0, s>>>(r, plan, n_q, n_kv, D, part, out);
+    else if (out_t == ACT_BF16) k_attn_combine<uint16_t><<<R * n_q, D, 0, s>>>(r, plan, n_q, n_kv, D, part, out);
+    else k_attn_combine<_Float16><<<R * n_q, D, 0, s>>>(r, plan, n_q, n_kv, D, part, out);
 }
 
 void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, hipStream_t s)
