@@ -209,26 +209,17 @@ static size_t gpart_bytes(const sd_model_cfg& c, int R)
 {
     if (c.dtype == SD_DTYPE_F32) return 256;
     size_t mx = 0;
-    for (int M = 1; M <= R; M = (M < 64 ? M + 1 : M + 64)) {
-        int m = M > R ? R : M;
+    for (int m = 1; m <= R; ++m) {
+        size_t f = gemm_part_floats(m, c.vocab, c.hidden);
+        mx = f > mx ? f : mx;
         for (int w = 0; w < 4; ++w) {
             int N, K;
             prj_shape(c, w, &N, &K);
-            size_t f = gemm_part_floats(m, N, K);
+            f = gemm_part_floats(m, N, K);
             mx = f > mx ? f : mx;
             f = gemm_q4_part_floats(m, N, K);
             mx = f > mx ? f : mx;
         }
-        size_t f = gemm_part_floats(m, c.vocab, c.hidden);
-        mx = f > mx ? f : mx;
-    }
-    for (int w = 0; w < 4; ++w) {
-        int N, K;
-        prj_shape(c, w, &N, &K);
-        size_t f = gemm_part_floats(R, N, K);
-        mx = f > mx ? f : mx;
-        f = gemm_q4_part_floats(R, N, K);
-        mx = f > mx ? f : mx;
     }
     return (mx > 64 ? mx : 64) * 4;
 }

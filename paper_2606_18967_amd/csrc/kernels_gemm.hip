@@ -1,11 +1,10 @@
 // kernels_gemm.hip -- the bf16 projections: C[M][N] (fp32) = or += A[M][K] W^T.
 //
 // Weights are row-major [N][K] (K contiguous), activations [M][K].
-//   - gemm_dma64 (M <= 64, N a multiple of 256): 64-row tiles with both
-//     operands brought into LDS by DMA through a three-stage ring; see
-//     k_gemm_dma64.  gemm_stream (M <= 64, other N): weights streamed from
-//     HBM into registers, v_mfma_f32_16x16x32_bf16; see k_gemm_stream.
-//   - gemm_tiled (M > 64, the verify forward): both operands through LDS.
+//   - gemm_dma (N a multiple of 256, beyond 64 rows of 128): tiles of 64 to
+//     320 rows, both operands brought into LDS by DMA; see k_gemm_dma.
+//   - gemm_stream (other N): weights streamed from HBM into registers,
+//     v_mfma_f32_16x16x32_bf16; see k_gemm_stream.
 //   - gemm_f32 / gemm_q4_f32: plain VALU versions for fp32 models (the int4
 //     one reads the packed layout of kernels_q4.hip).
 #include "common.h"
@@ -210,124 +209,17 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restr
     }
 }
 
-// ------------------------------------------------------------------ tiled bf16 MFMA GEMM (M > 64)
-// C[M][N] = A[M][K] W^T with both operands staged through LDS.  Block tile
-// (32*MTW) x 128, four waves in a 2 x 2 grid, each wave (16*MTW) x 64 =
-// MTW x 4 MFMA tiles of v_mfma_f32_16x16x32_bf16.  K advances in stages of 64
-// with double-buffered LDS and the global loads of stage k + 2 in flight while
-// stage k is multiplied.  LDS rows are padded to 72 elements (bank-conflict
-// free 16-byte fragment reads).  Split-K partials as in k_gemm_stream.
+// ------------------------------------------------------------------ tiled bf16 MFMA GEMM, register-staged
+// C[M][N] = A[M][K] W^T with both operands staged through registers into LDS:
+// the reference form of the 320-row DMA-fed tiles below (debug switch).  Block
+// tile (32*MTW) x 128, four waves in a 2 x 2 grid, each wave (16*MTW) x 64 =
+// MTW/2 x 2 blocks of v_mfma_f32_32x32x16_bf16; lane l reads row or column
+// l % 32 and k 8 (l / 32) + 0..7 of each 16-k step.  K advances in stages of
+// 64 with double-buffered LDS and the global loads of stage k + 2 in flight
+// while stage k is multiplied.  LDS rows are padded to 72 elements (bank-
+// conflict free 16-byte fragment reads).  Split-K partials as in k_gemm_stream.
 constexpr int TBK = 64, TLD = TBK + 8, TBN = 128;
 
-template <int MTW>
-__global__ void __launch_bounds__(256) k_gemm_tiled(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                    float* __restrict__ C, float* __restrict__ P, int M, int N, int K,
-                                                    int ldc, int mode, int S, int mtiles, int total)
-{
-    constexpr int BM = 32 * MTW;
-    constexpr int AP = MTW;      // 16-byte A pieces per thread per stage (BM*8/256)
-    constexpr int WP = 4;        // 16-byte W pieces per thread per stage (128*8/256)
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][BM * TLD];
-    __shared__ __attribute__((aligned(16))) uint16_t Ws[2][TBN * TLD];
-    const int per_xcd = gridDim.x >> 3;
-    const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (w >= total) return;
-    const int mt = w % mtiles, rest = w / mtiles;
-    const int s = rest % S, nt = rest / S;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wm = wv >> 1, wn = wv & 1;
-    const int m0 = mt * BM, n0 = nt * TBN;
-    const int KS = K / TBK, Ks = KS / S, k0 = s * Ks, k1 = k0 + Ks;
-    const int rows = min(M - m0, BM);
-
-    u32x4 ra[2][AP], rw[2][WP];
-    auto load = [&](int kb, u32x4 (&a)[AP], u32x4 (&b)[WP]) {
-#pragma unroll
-        for (int t = 0; t < AP; ++t) {
-            const int pidx = tid + t * 256, row = pidx >> 3, col = (pidx & 7) * 8;
-            a[t] = *(const u32x4*)(A + (size_t)(m0 + min(row, rows - 1)) * K + (size_t)kb * TBK + col);
-        }
-#pragma unroll
-        for (int t = 0; t < WP; ++t) {
-            const int pidx = tid + t * 256, row = pidx >> 3, col = (pidx & 7) * 8;
-            b[t] = *(const u32x4*)(W + (size_t)(n0 + row) * K + (size_t)kb * TBK + col);
-        }
-    };
-    auto store = [&](int buf, const u32x4 (&a)[AP], const u32x4 (&b)[WP]) {
-#pragma unroll
-        for (int t = 0; t < AP; ++t) {
-            const int pidx = tid + t * 256, row = pidx >> 3, col = (pidx & 7) * 8;
-            *(u32x4*)(&As[buf][row * TLD + col]) = row < rows ? a[t] : (u32x4){0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int t = 0; t < WP; ++t) {
-            const int pidx = tid + t * 256, row = pidx >> 3, col = (pidx & 7) * 8;
-            *(u32x4*)(&Ws[buf][row * TLD + col]) = b[t];
-        }
-    };
-
-    floatx4 acc[MTW][4];
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-
-    load(k0, ra[0], rw[0]);
-    if (k0 + 1 < k1) load(k0 + 1, ra[1], rw[1]);
-    store(0, ra[0], rw[0]);
-    lds_barrier();
-    for (int kb = k0; kb < k1; kb += 2) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int k = kb + u;
-            if (k < k1) {
-                const int buf = (k - k0) & 1;
-                if (k + 2 < k1) load(k + 2, ra[u], rw[u]);      // slot u is free: stage k is in LDS
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const int kk = ks * 32 + (lane >> 4) * 8;
-                    u32x4 af[MTW], bw[4];
-#pragma unroll
-                    for (int i = 0; i < MTW; ++i)
-                        af[i] = *(const u32x4*)(&As[buf][(wm * 16 * MTW + 16 * i + (lane & 15)) * TLD + kk]);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        bw[j] = *(const u32x4*)(&Ws[buf][(wn * 64 + 16 * j + (lane & 15)) * TLD + kk]);
-#pragma unroll
-                    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[i]),
-                                                                               __builtin_bit_cast(bf16x8, bw[j]),
-                                                                               acc[i][j], 0, 0, 0);
-                }
-                if (k + 1 < k1) store(buf ^ 1, ra[u ^ 1], rw[u ^ 1]);
-                lds_barrier();
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = n0 + wn * 64 + 16 * j + (lane & 15);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + wm * 16 * MTW + 16 * i + (lane >> 4) * 4 + r;
-                if (row >= M) continue;
-                if (S == 1) {
-                    float* cp = C + (size_t)row * ldc + col;
-                    *cp = mode == GEMM_ADD ? *cp + acc[i][j][r] : acc[i][j][r];
-                } else {
-                    P[((size_t)s * M + row) * N + col] = acc[i][j][r];
-                }
-            }
-        }
-}
-
-// The same tiling on v_mfma_f32_32x32x16_bf16 (MTW even): each wave's
-// (16 MTW) x 64 tile is MTW/2 x 2 blocks of 32 x 32; lane l reads row or
-// column l % 32 and k 8 (l / 32) + 0..7 of each 16-k step.
 // SW: the SwiGLU epilogue.  W is [2F][K], gate rows then up rows; column tile
 // t loads gate rows 64t..64t+63 (waves wn = 0) and up rows F + 64t.. (wn = 1),
 // runs without split-K and writes out[m][f] = SiLU(g) u (type out_t).
@@ -447,8 +339,7 @@ __global__ void __launch_bounds__(256) k_gemm_t32(const uint16_t* __restrict__ A
                 for (int r = 0; r < 16; ++r) {
                     const int row = m0 + wm * 16 * MTW + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                     if (row >= M) continue;
-                    const float g = acc[i][j][r], u = ys[yi(i, j, r)];
-                    const float v = g / (1.f + __expf(-g)) * u;
+                    const float v = swiglu(acc[i][j][r], ys[yi(i, j, r)]);
                     const size_t oi = (size_t)row * F + feat;
                     if (out_t == ACT_F16) store_act<_Float16>(out, oi, v);
                     else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, v);
@@ -476,23 +367,27 @@ __global__ void __launch_bounds__(256) k_gemm_t32(const uint16_t* __restrict__ A
         }
 }
 
-// ------------------------------------------------------------------ 320-row tiles fed by LDS DMA
-// The 320-row tile of k_gemm_t32 (wave tile 160 x 64, v_mfma_f32_32x32x16_bf16,
-// the same MFMA operands in the same k order, so the same fp32 sums) with the
-// operands brought into LDS by global_load_lds_dwordx4: each instruction puts
-// 64 lanes x 16 bytes straight into 1 KB of LDS, so no registers stage the
-// tiles and the waves issue no LDS stores.  K advances in stages of 64 through
-// two LDS buffers: stage k + 1 is requested right after the barrier that opens
-// stage k.  A stage holds 128-byte rows (64 k) of the A and W tiles; the
-// 16-byte chunk c of row r sits at position c ^ sw(r), sw(r) = (r ^ r / 8) % 8,
-// which keeps the fragment reads (rows r..r+7 or r..r+15 at one chunk) free of
-// bank conflicts; a DMA lane therefore fetches chunk pos ^ sw(r) of its row.
-// WN = 2: 320 x 128 tiles, 4 waves; WN = 4: 320 x 256 tiles, 8 waves (half the
-// activation re-reads per weight byte, for launches with a full wave of tiles).
-// SW: the SwiGLU epilogue; the tile takes 32 WN features, and wave column
+// ------------------------------------------------------------------ tiles fed by LDS DMA
+// C[M][N] = A[M][K] W^T, tile (32 MT) x (64 WCN), WM x WCN waves, each wave
+// (32 MT / WM) x 64 as MT / WM x 2 blocks of v_mfma_f32_32x32x16_bf16 (k in
+// ascending 16-k steps).  Both operands come into LDS by
+// global_load_lds_dwordx4: an instruction puts 64 lanes x 16 bytes straight
+// into 1 KB of LDS, whole 128-byte lines of eight rows, so no registers stage
+// the tiles and the waves issue no LDS stores.  K advances in stages of 64
+// through a ring of NST buffers: NST - 1 stages are in flight, the next one
+// requested right after the barrier that opens a stage.  The 16-byte chunk c
+// of row r sits at position c ^ sw(r), sw(r) = (r ^ r / 8) % 8, which keeps the
+// fragment reads (rows r..r+7 or r..r+15 at one chunk) free of bank conflicts;
+// a DMA lane therefore fetches chunk pos ^ sw(r) of its row.  Rows past M
+// repeat row M - 1 (never stored).
+// SW: the SwiGLU epilogue; the tile takes 32 WCN features, and wave column
 // wn's two 32-column blocks are the gate rows and the up rows of the same 32
 // features, so SiLU(g) u is formed in registers (no split-K there).  With S
-// K splits the partial sums go to P[s][M][N] as in k_gemm_t32.
+// K splits the partial sums go to P[s][M][N] as in k_gemm_stream.
+// Weights read by one m-tile only are non-temporal.
+// What bounds it: the weights' stream up to about 200 rows, so the ring is as
+// deep as LDS allows (three stages of 160 x 256 are 156 KB); the matrix cores
+// and the wait for the next stage at 320 rows (two stages).
 constexpr int DBK = 64, DRB = DBK * 2;                  // k per stage, bytes per tile row
 
 __device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds_byte)
@@ -514,32 +409,46 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// The stage a tile starts its K range with (it goes round).  Rows are K
+// elements apart, so at one k all rows of all tiles lie in the same few memory
+// channels; tiles that walk K in step crowd them (8B gate/up at M = 64: 49 ->
+// 43 us; no difference at 128 rows and more).  The gate and the up
+// columns of a feature start alike, in the plain form and in the SwiGLU form
+// (whose tile takes half as many features), so that both sum in one order.
+__device__ __forceinline__ int dma_rot(int nt, int s, int tiles, int Ks, bool sw)
+{
+    const int t = sw ? nt >> 1 : (tiles % 2 == 0 && nt >= tiles / 2 ? nt - tiles / 2 : nt);
+    return tiles % 2 ? 0 : (t * 5 + s) % Ks;
+}
+
 __device__ __forceinline__ int dma_sw(int r) { return (r ^ (r >> 3)) & 7; }
 
-template <int WN, bool SW>
-__global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                       float* __restrict__ C, float* __restrict__ P, int M, int N, int K,
-                                                       int ldc, int mode, int S, int mtiles, int total,
-                                                       void* __restrict__ out, int out_t)
+template <int MT, int WM, int WCN, int NST, bool SW>
+__global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+                                                            float* __restrict__ C, float* __restrict__ P, int M, int N,
+                                                            int K, int ldc, int mode, int S, int mtiles, int total,
+                                                            void* __restrict__ out, int out_t)
 {
-    constexpr int MTW = 10, BM = 32 * MTW, BN = 64 * WN, NWAVE = 2 * WN;
+    constexpr int BM = 32 * MT, BN = 64 * WCN, NWAVE = WM * WCN, RT = MT / WM;   // RT row blocks per wave
     constexpr int NA = BM / 8, NI = NA + BN / 8;               // 1 KB pieces (8 rows) per stage
     constexpr int STG = (BM + BN) * DRB;
     constexpr int CNT = NI / NWAVE;                            // pieces per wave per stage
-    static_assert(NI % NWAVE == 0, "every wave issues the same number of pieces");
-    constexpr int FT = 32 * WN;                                // features per tile of the SwiGLU form
-    __shared__ __attribute__((aligned(1024))) uint8_t sm[2 * STG];
+    static_assert(MT % WM == 0 && NI % NWAVE == 0, "every wave has the same rows and pieces");
+    static_assert(NST >= 2 && NST <= 5 && NST * STG <= 160 * 1024 && CNT * (NST - 2) < 64, "LDS, vmcnt");
+    constexpr int FT = 32 * WCN;                               // features per tile of the SwiGLU form
+    __shared__ __attribute__((aligned(1024))) uint8_t sm[NST * STG];
     const uint32_t sbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)sm;
-    const int per_xcd = gridDim.x >> 3;
+    const int per_xcd = gridDim.x >> 3;                        // gridDim.x is a multiple of 8
     const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (w >= total) return;
     const int mt = w % mtiles, rest = w / mtiles;
     const int s = rest % S, nt = rest / S;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wv / WN, wn = wv % WN;
+    const int wm = wv / WCN, wn = wv % WCN;
     const int m0 = mt * BM, n0 = nt * BN;
     const int Ks = K / DBK / S, k0 = s * Ks;
     const int rows = min(M - m0, BM);
+    const bool once = mtiles == 1;                             // no other m-tile reads these weights
 
     // this lane's source row and chunk for each of its pieces
     const uint16_t* src[CNT];
@@ -562,36 +471,46 @@ __global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restric
             dst[q] = BM * DRB + (t - NA) * 1024;
         }
     }
-    auto issue = [&](int buf, int kb) {
+    const int rot = MT == 10 ? 0 : dma_rot(nt, s, N / BN, Ks, SW);
+    auto issue = [&](int kb) {
+        const uint32_t buf = sbase + (kb % NST) * STG;
+        const size_t at = (size_t)(kb + rot < Ks ? kb + rot : kb + rot - Ks) * DBK;
 #pragma unroll
         for (int q = 0; q < CNT; ++q) {
-            if (wv + q * NWAVE < NA) lds_dma16(src[q] + (size_t)kb * DBK, sbase + buf * STG + dst[q]);
-            else lds_dma16_nt(src[q] + (size_t)kb * DBK, sbase + buf * STG + dst[q]);
+            if (wv + q * NWAVE >= NA && once) lds_dma16_nt(src[q] + at, buf + dst[q]);
+            else lds_dma16(src[q] + at, buf + dst[q]);
         }
     };
 
-    floatx16 acc[MTW / 2][2];
+    floatx16 acc[RT][2];
 #pragma unroll
-    for (int i = 0; i < MTW / 2; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    issue(0, 0);
+#pragma unroll
+    for (int u = 0; u < NST - 1; ++u)
+        if (u < Ks) issue(u);
     for (int kb = 0; kb < Ks; ++kb) {
-        wait_vmcnt<0>();                    // this wave's pieces of stage kb are in LDS
+        // this wave's pieces of stage kb are in once those of the later stages are all that is outstanding
+        const int later = min(NST - 2, Ks - 1 - kb);
+        if (NST >= 5 && later == 3) wait_vmcnt<3 * CNT>();
+        else if (NST >= 4 && later == 2) wait_vmcnt<2 * CNT>();
+        else if (NST >= 3 && later == 1) wait_vmcnt<CNT>();
+        else wait_vmcnt<0>();
         lds_barrier();                      // everyone's are, and stage kb - 1 is no longer read
-        if (kb + 1 < Ks) issue((kb + 1) & 1, kb + 1);
-        const uint8_t* sa = sm + (kb & 1) * STG;
+        if (kb + NST - 1 < Ks) issue(kb + NST - 1);
+        const uint8_t* sa = sm + (kb % NST) * STG;
         const uint8_t* sw = sa + BM * DRB;
 #pragma unroll
         for (int ks = 0; ks < DBK / 16; ++ks) {
             const int c = 2 * ks + (lane >> 5);
-            u32x4 af[MTW / 2], bw[2];
+            u32x4 af[RT], bw[2];
 #pragma unroll
-            for (int i = 0; i < MTW / 2; ++i) {
-                const int r = wm * 16 * MTW + 32 * i + (lane & 31);
+            for (int i = 0; i < RT; ++i) {
+                const int r = (wm * RT + i) * 32 + (lane & 31);
                 af[i] = *(const u32x4*)(sa + r * DRB + ((c ^ dma_sw(r)) << 4));
             }
 #pragma unroll
@@ -600,7 +519,7 @@ __global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restric
                 bw[j] = *(const u32x4*)(sw + r * DRB + ((c ^ dma_sw(r)) << 4));
             }
 #pragma unroll
-            for (int i = 0; i < MTW / 2; ++i)
+            for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i]),
@@ -611,13 +530,12 @@ __global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restric
     if constexpr (SW) {
         const int F = N / 2, feat = nt * FT + wn * 32 + (lane & 31);
 #pragma unroll
-        for (int i = 0; i < MTW / 2; ++i)
+        for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm * 16 * MTW + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int row = m0 + (wm * RT + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (row >= M) continue;
-                const float g = acc[i][0][r], u = acc[i][1][r];
-                const float v = g / (1.f + __expf(-g)) * u;
+                const float v = swiglu(acc[i][0][r], acc[i][1][r]);
                 const size_t oi = (size_t)row * F + feat;
                 if (out_t == ACT_F16) store_act<_Float16>(out, oi, v);
                 else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, v);
@@ -626,13 +544,13 @@ __global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restric
         return;
     }
 #pragma unroll
-    for (int i = 0; i < MTW / 2; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int col = n0 + wn * 64 + 32 * j + (lane & 31);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm * 16 * MTW + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int row = m0 + (wm * RT + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (row >= M) continue;
                 if (S == 1) {
                     float* cp = C + (size_t)row * ldc + col;
@@ -642,138 +560,6 @@ __global__ void __launch_bounds__(128 * WN) k_gemm_dma(const uint16_t* __restric
                 }
             }
         }
-}
-
-// ------------------------------------------------------------------ 64-row tiles fed by LDS DMA
-// The decode-shaped GEMM (M <= 64: the AR step's projections, the draft LM
-// head) as a 64 x 256 tile of the DMA-fed kernel above: eight waves, each a
-// 32 x 64 block of v_mfma_f32_32x32x16_bf16, operands brought into LDS by
-// global_load_lds_dwordx4 in whole 128-byte lines.  At 64 rows the tile
-// computes little per stage, so the ring is three stages deep (two in
-// flight while one is multiplied; 120 KB of LDS).  Streaming the weights
-// straight into registers in the MFMA layout (k_gemm_stream) reads 64 bytes
-// from each of 16 rows 10 KB apart per instruction and reaches 2.3-4.3 TB/s
-// at the 32B shape's projections; this tile reaches 3.7-6.0 TB/s (gate/up
-// 137 -> 95 us, down 85 -> 49 us, LM head 368 -> 309 us at M = 64).  Rows past
-// M repeat row M - 1 (never stored); split-K partials as in k_gemm_dma.  SW:
-// the SwiGLU epilogue of k_gemm_dma (a tile of 128 features; wave column
-// wn's two 32-column blocks are the gate and the up rows of the same 32
-// features), used where the gate/up projection runs unsplit.
-constexpr int D64R = 3;                                 // LDS ring stages
-
-template <bool SW>
-__global__ void __launch_bounds__(512) k_gemm_dma64(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                    float* __restrict__ C, float* __restrict__ P, int M, int N, int K,
-                                                    int ldc, int mode, int S, int total, void* __restrict__ out,
-                                                    int out_t)
-{
-    constexpr int BM = 64, BN = 256, NWAVE = 8, NB = D64R;
-    constexpr int NA = BM / 8, NI = NA + BN / 8;            // 1 KB pieces (8 rows of 128 B) per stage
-    constexpr int STG = (BM + BN) * DRB;
-    constexpr int CNT = NI / NWAVE;
-    static_assert(NI % NWAVE == 0 && NB == 3, "five pieces per wave, waits written for three stages");
-    __shared__ __attribute__((aligned(1024))) uint8_t sm[NB * STG];
-    const uint32_t sbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)sm;
-    const int per_xcd = gridDim.x >> 3;                     // gridDim.x is a multiple of 8
-    const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (w >= total) return;
-    const int s = w % S, nt = w / S;
-    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wv >> 2, wn = wv & 3;
-    const int n0 = nt * BN;
-    const int Ks = K / DBK / S, k0 = s * Ks;
-
-    const uint16_t* src[CNT];
-    uint32_t dst[CNT];
-#pragma unroll
-    for (int q = 0; q < CNT; ++q) {
-        const int t = wv + q * NWAVE, rl = lane >> 3, pos = lane & 7;
-        if (t < NA) {
-            const int row = 8 * t + rl;
-            src[q] = A + (size_t)min(row, M - 1) * K + (size_t)k0 * DBK + 8 * (pos ^ dma_sw(row));
-            dst[q] = t * 1024;
-        } else {
-            const int row = 8 * (t - NA) + rl;
-            int wrow = n0 + row;
-            if constexpr (SW) {
-                const int f = nt * (BN / 2) + (row >> 6) * 32 + (row & 31);   // wave column row/64, block (row/32)%2
-                wrow = ((row >> 5) & 1) ? N / 2 + f : f;
-            }
-            src[q] = W + (size_t)wrow * K + (size_t)k0 * DBK + 8 * (pos ^ dma_sw(row));
-            dst[q] = BM * DRB + (t - NA) * 1024;
-        }
-    }
-    auto issue = [&](int buf, int kb) {
-#pragma unroll
-        for (int q = 0; q < CNT; ++q) {
-            if (wv + q * NWAVE < NA) lds_dma16(src[q] + (size_t)kb * DBK, sbase + buf * STG + dst[q]);
-            else lds_dma16_nt(src[q] + (size_t)kb * DBK, sbase + buf * STG + dst[q]);
-        }
-    };
-
-    floatx16 acc[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-
-    issue(0, 0);
-    if (Ks > 1) issue(1, 1);
-    for (int kb = 0; kb < Ks; ++kb) {
-        // this wave's pieces of stage kb are in once those of the (at most one) later stage are all that is outstanding
-        if (kb + 1 < Ks) wait_vmcnt<CNT>();
-        else wait_vmcnt<0>();
-        lds_barrier();                      // everyone's are, and stage kb - 1 is no longer read
-        if (kb + 2 < Ks) issue((kb + 2) % NB, kb + 2);
-        const uint8_t* sa = sm + (kb % NB) * STG;
-        const uint8_t* sw = sa + BM * DRB;
-#pragma unroll
-        for (int ks = 0; ks < DBK / 16; ++ks) {
-            const int c = 2 * ks + (lane >> 5);
-            const int ra = wm * 32 + (lane & 31);
-            const u32x4 af = *(const u32x4*)(sa + ra * DRB + ((c ^ dma_sw(ra)) << 4));
-            u32x4 bw[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int r = wn * 64 + 32 * j + (lane & 31);
-                bw[j] = *(const u32x4*)(sw + r * DRB + ((c ^ dma_sw(r)) << 4));
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af),
-                                                                 __builtin_bit_cast(bf16x8, bw[j]), acc[j], 0, 0, 0);
-        }
-    }
-    if constexpr (SW) {
-        const int F = N / 2, feat = nt * (BN / 2) + wn * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (row >= M) continue;
-            const float g = acc[0][r], u = acc[1][r];
-            const float v = g / (1.f + __expf(-g)) * u;
-            const size_t oi = (size_t)row * F + feat;
-            if (out_t == ACT_F16) store_act<_Float16>(out, oi, v);
-            else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, v);
-            else store_act<float>(out, oi, v);
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 64 + 32 * j + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (row >= M) continue;
-            if (S == 1) {
-                float* cp = C + (size_t)row * ldc + col;
-                *cp = mode == GEMM_ADD ? *cp + acc[j][r] : acc[j][r];
-            } else {
-                P[((size_t)s * M + row) * N + col] = acc[j][r];
-            }
-        }
-    }
 }
 
 // C[m][n] (+)= sum_s P[s][m][n]
@@ -852,121 +638,99 @@ void gemm_plan(int M, int N, int K, int* nbw, int* S)
     *S = s;
 }
 
-// bf16 GEMMs with more than 64 rows use the tiled kernel (N % 128 == 0).
-static bool use_tiled(int M, int N, int K) { return M > 64 && N % TBN == 0 && K % TBK == 0; }
+// The DMA-fed tiles' plan: tile height 32 mt, width 64 wcn, S splits of the
+// K / 64 stages.
+struct dma_tile { int mt, wcn, S; };
 
-// Tile height of the LDS-tiled kernels, in units of 32 rows: the height with
-// the fewest padded rows ceil(M / BM) BM, ties going to the taller tile, since
-// every m-tile reads the whole weight matrix again.  Heights 320, 256, 192 and
-// 128 rows are k_gemm_t32<10|8|6|4> (32x32x16 MFMAs), 160 rows k_gemm_tiled<5>
-// (16x16x32).  At M = 320 (64 sequences, gamma = 4) one 320-row tile reads each
-// weight tile once: -15% on the four projections of a layer against two 160-
-// or three 128-row tiles.
-static int tiled_mtw(int M)
-{
-    static const int cand[] = {10, 8, 6, 5, 4};
-    int best = 4;
-    long best_rows = -1;
-    for (int m : cand) {
-        const long rows = (long)((M + 32 * m - 1) / (32 * m)) * 32 * m;
-        if (best_rows < 0 || rows < best_rows) best = m, best_rows = rows;
-    }
-    return best;
-}
+// N a multiple of 128, K of 64 (at least two stages)
+static bool use_dma(int N, int K) { return N % 128 == 0 && K % DBK == 0 && K >= 2 * DBK; }
 
-// The height every form of the tiled GEMM takes.  Past 320 rows the 320-row
-// tiles fed by LDS DMA win even where they pad: fewer passes over the weights
-// at a higher rate per pass (measured at N = 28672, K = 4096: 142 against
-// 158 us at M = 330, 144 against 228 us at M = 448; 894 against 537 TFLOP/s
-// at 8192^3).  Up to 320 rows the tightest height stays (at 96-256 rows the
-// shorter tiles are faster).
-static int gemm_mtw(int M) { return M > 320 ? 10 : tiled_mtw(M); }
-
-#ifndef TILED_SPLIT_TARGET
-#define TILED_SPLIT_TARGET 192
-#endif
-
-static void tiled_plan(int M, int N, int K, int* mtw, int* S)
-{
-    *mtw = gemm_mtw(M);
-    int mtiles = (M + 32 * *mtw - 1) / (32 * *mtw);
-    int tiles = N / TBN * mtiles;
-    int KS = K / TBK;
-    int s = 1;
-    while (tiles * s < TILED_SPLIT_TARGET && KS % (2 * s) == 0 && KS / (2 * s) >= 4 && 2 * s <= GEMM_MAX_SPLIT) s *= 2;
-    *S = s;
-}
-
-// 320-row tiles: without a K split where 320 x 256 tiles (eight waves, half
-// the activation bytes per weight byte of 320 x 128) or else 320 x 128 tiles
-// give DMA_SPLIT_TARGET work-groups; otherwise 320 x 256 tiles (where N
-// allows) and the smallest split S of the K / 64 stages (at least two per
-// split, at most DMA_MAX_SPLIT) that gives that many.  The register-staged
-// tiles and the SwiGLU form take the same S, so every form sums the same
-// products in the same order.
-#ifndef DMA_SPLIT_TARGET
-#define DMA_SPLIT_TARGET 192
-#endif
 #ifndef DMA_MAX_SPLIT
 #define DMA_MAX_SPLIT 32
 #endif
 
-static void dma_plan(int M, int N, int K, int* wn, int* S)
+// Height: the lowest of 64, 96, 128, 160, 192, 256 and 320 rows that holds M;
+// more rows take 320-row tiles (fewer passes over the weights at a higher rate
+// per pass: 8B gate/up at 640 rows 154 us, in 256-row tiles 236).  Width and
+// split: the least of rounds of 256 work-groups x (stages + 3 to start) x a
+// stage's time, plus, with splits, 8 us and the partial sums' write and read at
+// 5 TB/s (an unsplit gate/up forms SwiGLU in its epilogue).
+// A stage of 128 columns takes about .42 + .125 mt us with all CUs at work
+// (measured .67, .9, 1.4 and 1.7 at mt 2, 4, 8 and 10), one of 256 columns
+// 1.65 times that: half as many activation bytes per weight, but half as many
+// work-groups, so wide tiles go to large N (LM head at M = 128: 195 against
+// 283 us), narrow ones elsewhere (8B gate/up at M = 128: 58 against 71; down
+// projections with half the splits).  Heights of 96 and 160 rows are built at
+// 256 columns only (LM head at M = 148: 214 us, in a 192-row tile 241).
+static dma_tile dma_plan(int M, int N, int K)
 {
-    const int mtiles = (M + 319) / 320;
-    *S = 1;
-    if (N % 256 == 0 && N / 256 * mtiles >= DMA_SPLIT_TARGET) { *wn = 4; return; }
-    if (N / 128 * mtiles >= DMA_SPLIT_TARGET) { *wn = 2; return; }
-    *wn = N % 256 == 0 ? 4 : 2;
-    const int tiles = N / (64 * *wn) * mtiles;
-    const int KB = K / 64;
-    for (int s = 1; s <= DMA_MAX_SPLIT && 2 * s <= KB; ++s) {
-        if (KB % s) continue;
-        *S = s;
-        if (tiles * s >= DMA_SPLIT_TARGET) break;
+    const int KB = K / DBK;
+    dma_tile best = {0, 0, 1};
+    double least = 0;
+    for (int wcn = 4; wcn >= 2; wcn -= 2) {
+        if (N % (64 * wcn)) continue;
+        int mt = M <= 64 ? 2 : M > 256 ? 10 : M > 192 ? 8 : M > 160 ? 6 : (M + 31) / 32;
+        if (wcn == 2 && mt % 2) ++mt;
+        const long long tiles = (long long)(N / (64 * wcn)) * ((M + 32 * mt - 1) / (32 * mt));
+        const double stage = (.42 + .125 * mt) * (wcn == 4 ? 1.65 : 1.);
+        for (int S = 1; S <= DMA_MAX_SPLIT && 2 * S <= KB; ++S) {
+            if (KB % S) continue;
+            const double wgs = (double)tiles * S, rounds = wgs <= 256 ? 1. : wgs / 256 + .35;
+            const double t = rounds * (KB / S + 3) * stage + (S > 1 ? 8 + 8e-6 / 5 * S * M * N : 0.);
+            if (!best.mt || t < least) best = {mt, wcn, S}, least = t;
+        }
     }
-}
-
-// the 64-row DMA tiles: N a multiple of 256, K of 64 (at least two stages)
-static bool use_dma64(int M, int N, int K) { return M <= 64 && N % 256 == 0 && K % DBK == 0 && K >= 2 * DBK; }
-
-#ifndef DMA64_SPLIT_TARGET
-#define DMA64_SPLIT_TARGET 192
-#endif
-
-// split count of the 64-row tiles: the smallest divisor S of the K / 64
-// stages (at least two stages per split, at most 32 splits) giving
-// DMA64_SPLIT_TARGET work-groups, else the largest such S
-static int dma64_split(int N, int K)
-{
-    const int tiles = N / 256, KB = K / DBK;
-    int S = 1;
-    for (int s = 1; s <= 32 && 2 * s <= KB; ++s) {
-        if (KB % s) continue;
-        S = s;
-        if (tiles * s >= DMA64_SPLIT_TARGET) break;
-    }
-    return S;
+    return best;
 }
 
 size_t gemm_part_floats(int M, int N, int K)
 {
     int nbw, S;
     gemm_plan(M, N, K, &nbw, &S);
-    if (use_dma64(M, N, K)) {
-        const int S64 = dma64_split(N, K);
-        S = S64 > S ? S64 : S;
-    }
-    if (use_tiled(M, N, K)) {
-        int mtw, St;
-        tiled_plan(M, N, K, &mtw, &St);
-        if (mtw == 10) {
-            int wn;
-            dma_plan(M, N, K, &wn, &St);
-        }
-        S = St > S ? St : S;
-    }
+    if (use_dma(N, K)) S = dma_plan(M, N, K).S;
     return S > 1 ? (size_t)S * M * N : 0;
+}
+
+// args of k_gemm_dma, launched as the plan's instance
+struct dma_args {
+    const uint16_t *A, *W;
+    float *C, *P;
+    int M, N, K, ldc, mode;
+    void* out;
+    int out_t;
+};
+
+template <int MT, int WM, int WCN, int NST, bool SW>
+static void dma_go(const dma_args& a, int S, hipStream_t s)
+{
+    const int mtiles = (a.M + 32 * MT - 1) / (32 * MT);
+    const int total = a.N / (64 * WCN) * mtiles * S;
+    k_gemm_dma<MT, WM, WCN, NST, SW><<<dim3((total + 7) / 8 * 8), 64 * WM * WCN, 0, s>>>(
+        a.A, a.W, a.C, a.P, a.M, a.N, a.K, a.ldc, a.mode, S, mtiles, total, a.out, a.out_t);
+}
+
+template <bool SW>
+static void dma_launch(const dma_args& a, dma_tile p, hipStream_t s)
+{
+    if (p.wcn == 4) {
+        switch (p.mt) {
+            case 2: dma_go<2, 2, 4, 3, SW>(a, p.S, s); break;
+            case 3: dma_go<3, 1, 4, 3, SW>(a, p.S, s); break;
+            case 4: dma_go<4, 2, 4, 3, SW>(a, p.S, s); break;
+            case 5: dma_go<5, 1, 4, 3, SW>(a, p.S, s); break;
+            case 6: dma_go<6, 2, 4, 2, SW>(a, p.S, s); break;
+            case 8: dma_go<8, 2, 4, 2, SW>(a, p.S, s); break;
+            default: dma_go<10, 2, 4, 2, SW>(a, p.S, s); break;
+        }
+    } else {
+        switch (p.mt) {
+            case 2: dma_go<2, 2, 2, 5, SW>(a, p.S, s); break;
+            case 4: dma_go<4, 2, 2, 5, SW>(a, p.S, s); break;
+            case 6: dma_go<6, 2, 2, 3, SW>(a, p.S, s); break;
+            case 8: dma_go<8, 2, 2, 3, SW>(a, p.S, s); break;
+            default: dma_go<10, 2, 2, 2, SW>(a, p.S, s); break;
+        }
+    }
 }
 
 template <int NBW, int NW>
@@ -982,55 +746,27 @@ static void stream_mt(int MT, dim3 grid, hipStream_t s, const uint16_t* A, const
     }
 }
 
+static void reduce_splits(const float* part, float* C, int M, int N, int ldc, int S, int mode, hipStream_t s)
+{
+    const size_t MN = (size_t)M * N;
+    k_splitk_reduce<<<(unsigned)((MN + 255) / 256), 256, 0, s>>>(part, C, M, N, ldc, S, mode);
+}
+
 int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part, size_t part_cap, int M, int N, int K,
                      int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma)
 {
-    if (use_tiled(M, N, K)) {
-        int mtw, S, wn = 2;
-        tiled_plan(M, N, K, &mtw, &S);
-        if (mtw == 10) dma_plan(M, N, K, &wn, &S);
-        if (S > 1 && (size_t)S * M * N > part_cap) S = 1;
-        int mtiles = (M + 32 * mtw - 1) / (32 * mtw);
-        if (lds_dma && mtw == 10) {
-            // 320-row tiles: the DMA-fed kernel
-            const int total = N / (64 * wn) * mtiles * S;
-            dim3 grid((total + 7) / 8 * 8);
-            if (wn == 4)
-                k_gemm_dma<4, false><<<grid, 512, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0);
-            else
-                k_gemm_dma<2, false><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0);
-            if (S > 1 && !defer_reduce) {
-                size_t MN = (size_t)M * N;
-                k_splitk_reduce<<<(unsigned)((MN + 255) / 256), 256, 0, s>>>(part, C, M, N, ldc, S, mode);
-            }
-            return S;
+    if (use_dma(N, K)) {
+        dma_tile p = dma_plan(M, N, K);
+        if (p.S > 1 && (size_t)p.S * M * N > part_cap) p.S = 1;   // workspace too small: no split
+        if (lds_dma || p.mt != 10) {
+            dma_launch<false>({A, W, C, part, M, N, K, ldc, mode, nullptr, 0}, p, s);
+        } else {
+            const int mtiles = (M + 319) / 320, total = N / TBN * mtiles * p.S;
+            k_gemm_t32<10, false><<<dim3((total + 7) / 8 * 8), 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, p.S, mtiles,
+                                                                            total, nullptr, 0);
         }
-        int total = N / TBN * mtiles * S;
-        dim3 grid((total + 7) / 8 * 8);
-        switch (mtw) {
-            case 10: k_gemm_t32<10, false><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0); break;
-            case 8: k_gemm_t32<8, false><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0); break;
-            case 6: k_gemm_t32<6, false><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0); break;
-            case 5: k_gemm_tiled<5><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total); break;
-            default: k_gemm_t32<4, false><<<grid, 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, mtiles, total, nullptr, 0); break;
-        }
-        if (S > 1 && !defer_reduce) {
-            size_t MN = (size_t)M * N;
-            k_splitk_reduce<<<(unsigned)((MN + 255) / 256), 256, 0, s>>>(part, C, M, N, ldc, S, mode);
-        }
-        return S;
-    }
-    if (use_dma64(M, N, K)) {
-        int S = dma64_split(N, K);
-        if (S > 1 && (size_t)S * M * N > part_cap) S = 1;   // workspace too small: no split
-        const int total = N / 256 * S;
-        k_gemm_dma64<false><<<dim3((total + 7) / 8 * 8), 512, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, total,
-                                                                       nullptr, 0);
-        if (S > 1 && !defer_reduce) {
-            size_t MN = (size_t)M * N;
-            k_splitk_reduce<<<(unsigned)((MN + 255) / 256), 256, 0, s>>>(part, C, M, N, ldc, S, mode);
-        }
-        return S;
+        if (p.S > 1 && !defer_reduce) reduce_splits(part, C, M, N, ldc, p.S, mode, s);
+        return p.S;
     }
     int nbw, S;
     gemm_plan(M, N, K, &nbw, &S);
@@ -1047,52 +783,25 @@ int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part
     if (wide) stream_mt<2, 8>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
     else if (nbw == 2) stream_mt<2, 4>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
     else stream_mt<1, 4>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
-    if (S > 1 && !defer_reduce) {
-        size_t MN = (size_t)M * N;
-        k_splitk_reduce<<<(unsigned)((MN + 255) / 256), 256, 0, s>>>(part, C, M, N, ldc, S, mode);
-    }
+    if (S > 1 && !defer_reduce) reduce_splits(part, C, M, N, ldc, S, mode, s);
     return S;
 }
 
 int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act_t out_t, int M, int F, int K,
                             hipStream_t s, bool lds_dma)
 {
-    if (use_dma64(M, 2 * F, K) && F % 128 == 0) {
-        // 64-row tiles: fused only where the plain projection runs unsplit
-        if (dma64_split(2 * F, K) != 1) return 0;
-        const int total = F / 128;
-        k_gemm_dma64<true><<<dim3((total + 7) / 8 * 8), 512, 0, s>>>(A, W, nullptr, nullptr, M, 2 * F, K, 0, 0, 1,
-                                                                      total, out, (int)out_t);
-        return 1;
-    }
-    if (!use_tiled(M, 2 * F, K) || F % 64) return 0;
-    const int mtw = gemm_mtw(M);
-    if (mtw == 5) return 0;                              // the 16x16x32 kernel has no SwiGLU epilogue
-    const int mtiles = (M + 32 * mtw - 1) / (32 * mtw);
-    const int total = F / 64 * mtiles;
-    dim3 grid((total + 7) / 8 * 8);
     const int N = 2 * F;
-    if (mtw == 10) {
-        // fused only where the plain projection would run unsplit (the same
-        // products summed in the same order either way)
-        int wn, S;
-        dma_plan(M, N, K, &wn, &S);
-        if (S != 1) return 0;
-        if (lds_dma) {
-            const int tot = F / (32 * wn) * mtiles;
-            dim3 g((tot + 7) / 8 * 8);
-            if (wn == 4)
-                k_gemm_dma<4, true><<<g, 512, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, tot, out, out_t);
-            else
-                k_gemm_dma<2, true><<<g, 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, tot, out, out_t);
-            return 1;
-        }
-    }
-    switch (mtw) {
-        case 10: k_gemm_t32<10, true><<<grid, 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, total, out, out_t); break;
-        case 8: k_gemm_t32<8, true><<<grid, 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, total, out, out_t); break;
-        case 6: k_gemm_t32<6, true><<<grid, 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, total, out, out_t); break;
-        default: k_gemm_t32<4, true><<<grid, 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles, total, out, out_t); break;
+    if (!use_dma(N, K) || F % 64) return 0;
+    // fused only where the plain projection runs unsplit (the same products
+    // summed in the same order either way)
+    const dma_tile p = dma_plan(M, N, K);
+    if (p.S != 1 || F % (32 * p.wcn)) return 0;
+    if (lds_dma || p.mt != 10) {
+        dma_launch<true>({A, W, nullptr, nullptr, M, N, K, 0, 0, out, (int)out_t}, p, s);
+    } else {
+        const int mtiles = (M + 319) / 320, total = F / 64 * mtiles;
+        k_gemm_t32<10, true><<<dim3((total + 7) / 8 * 8), 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles,
+                                                                       total, out, out_t);
     }
     return 1;
 }

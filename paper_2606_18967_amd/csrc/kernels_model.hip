@@ -83,7 +83,7 @@ constexpr int PLAN_SEQS = 512;      // sequences planned in LDS (more, always wh
 __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
 {
     __shared__ att_item s_it[PLAN_SEQS];
-    __shared__ int s_len[PLAN_SEQS], s_first[PLAN_SEQS];
+    __shared__ int s_len[PLAN_SEQS], s_nch[PLAN_SEQS], s_first[PLAN_SEQS];
     __shared__ int s_cnt[64], s_sum, s_top, s_items;
     const int tid = threadIdx.x, nt = blockDim.x;
     auto seq_of = [&](int b) {
@@ -135,7 +135,7 @@ __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
     }
     for (int b = tid; b < r.B; b += nt) {
         const int ctx = s_it[b].ctx, nch = max(1, (ctx + ch - 1) / ch);
-        s_it[b].nch = nch;
+        s_nch[b] = nch;
         s_len[b] = ((ctx + nch - 1) / nch + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT;   // <= ch: no chunk is empty
         atomicAdd(&s_items, nch);
     }
@@ -145,16 +145,18 @@ __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
     for (int t = tid; t < r.B * parts; t += nt) {
         const int b = t / parts, len = s_len[b];
         int first = 0;
+#pragma unroll 8
         for (int o = t - b * parts; o < r.B; o += parts) {
-            const int lo = s_len[o];
-            first += lo > len || (lo == len && o < b) ? s_it[o].nch : 0;
+            const int lo = s_len[o], no = s_nch[o];
+            first += lo > len || (lo == len && o < b) ? no : 0;
         }
         atomicAdd(&s_first[b], first);
     }
     __syncthreads();
     for (int b = tid; b < r.B; b += nt) {
         att_item it = s_it[b];
-        const int first = s_first[b], len = s_len[b], nch = it.nch;
+        const int first = s_first[b], len = s_len[b], nch = s_nch[b];
+        it.nch = nch;
         pl.seq[b] = make_int2(first, nch);
         for (int c = 0; c < nch && first + c < pl.max_items; ++c) {
             it.p0 = c * len;
@@ -1007,10 +1009,10 @@ __global__ void __launch_bounds__(256) k_silu_mul(const float* gu, const float* 
         u = add_splits(make_float4(0.f, 0.f, 0.f, 0.f), P, S, RN, ui);
     }
     const size_t o = (size_t)row * F + f;
-    store_act<O>(out, o, g.x / (1.f + __expf(-g.x)) * u.x);
-    store_act<O>(out, o + 1, g.y / (1.f + __expf(-g.y)) * u.y);
-    store_act<O>(out, o + 2, g.z / (1.f + __expf(-g.z)) * u.z);
-    store_act<O>(out, o + 3, g.w / (1.f + __expf(-g.w)) * u.w);
+    store_act<O>(out, o, swiglu(g.x, u.x));
+    store_act<O>(out, o + 1, swiglu(g.y, u.y));
+    store_act<O>(out, o + 2, swiglu(g.z, u.z));
+    store_act<O>(out, o + 3, swiglu(g.w, u.w));
 }
 
 // ------------------------------------------------------------------ kv length

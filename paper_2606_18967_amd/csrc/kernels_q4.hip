@@ -287,8 +287,7 @@ __global__ void __launch_bounds__(64 * QWAVES) k_gemm_q4(const uint16_t* __restr
             for (int r = 0; r < 16; ++r) {
                 const int row = m0 + t * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                 if (row >= M) continue;
-                const float g = acc[t][r], u = xs[((wv * MT + t) * 16 + r) * 64 + lane];
-                const float v = g / (1.f + __expf(-g)) * u;
+                const float v = swiglu(acc[t][r], xs[((wv * MT + t) * 16 + r) * 64 + lane]);
                 const size_t oi = (size_t)row * F + feat;
                 if (out_t == ACT_F16) store_act<_Float16>(out, oi, v);
                 else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, v);
