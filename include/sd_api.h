@@ -83,8 +83,10 @@ const char* sd_last_error(void);
 
 /* Creates an engine on the current HIP device.  max_slots: KV slots (and the
  * largest batch B); max_ctx: cached positions per slot; max_gamma: longest
- * draft.  The engine allocates its own workspace, sized for
- * max_slots*(max_gamma+1) rows. *out receives the handle. */
+ * draft.  The engine allocates its own workspace, sized for the larger of
+ * max_slots*(max_gamma+1) and 2560 rows (a prefill's; where
+ * memory has no room for those, the former). *out receives the
+ * handle. */
 sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32_t max_ctx, int32_t max_gamma,
                     sd_engine* out);
 sd_status sd_destroy(sd_engine e);
@@ -192,8 +194,7 @@ sd_status sd_prefill(sd_engine e, int32_t B, const int32_t* slots, const int32_t
  * int32[B][ld], row b's entries past len[b] are never read) of sequence
  * slots[b] at positions kv_len + i, then kv_len += len[b].  len: device
  * int32[B] with 0 <= len[b] <= ld.  The batch runs in rounds of a common
- * number of positions; a sequence whose prompt has ended computes padding
- * rows that are neither cached nor counted.  Errors: SD_E_INVAL (NULL
+ * number of positions, over the rows of the prompts that have not ended.  Errors: SD_E_INVAL (NULL
  * pointers, ld outside [1, max_ctx]), SD_E_STATE; a length outside [0, ld]
  * is reported by sd_sync (and that sequence is left unchanged), as are bad
  * slots, token ids and positions past max_ctx. */

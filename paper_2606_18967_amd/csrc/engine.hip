@@ -52,7 +52,8 @@ enum { T_ATTN_D = 0, T_ATTN_V = 1, T_Q4 = 2, T_PROJ = 3, T_LMHEAD = 4, T_SAMPLE 
 
 struct sd_engine_s {
     sd_model_cfg c;
-    int max_slots, max_ctx, max_gamma, rows_max;
+    int max_slots, max_ctx, max_gamma;
+    int rows_max;                // rows of one forward
     int dev;
     bool f32;
     int poison = 0;
@@ -84,7 +85,7 @@ struct sd_engine_s {
     float* acc_work = nullptr;
     float2* rope = nullptr;
     uint32_t* err = nullptr;
-    int32_t* pf_lim = nullptr;   // [max_slots] rows of one ragged-prefill round
+    int32_t* pf_lim = nullptr;   // a ragged-prefill round's lim [max_slots], row0 [max_slots] and live [1]
     float* gpart = nullptr;      // split-K partial sums
     size_t gpart_cap = 0;        // floats
     int launch_err = 0;          // a GEMM shape the kernels refused (reported by sd_sync)
@@ -232,6 +233,14 @@ static void free_ws(sd_engine e)
         if (p) (void)hipFree(p);
 }
 
+// Rows of one prefill forward, where a step has fewer: eight tiles of 320 rows
+// a pass over the weights (8B gate/up: 98 us and 690 TFLOP/s at the 288 rows of
+// 24 sequences drafting up to 11, 292 us and 1030 TFLOP/s at 1280; 24 prompts of
+// 170-511 tokens in 36.0, 20.1, 17.3 and 18.5 ms with 288, 1280, 2560 and 3840
+// rows).  The workspace this takes, .7 MB a row at the 32B shape, is 0.6% of
+// the memory; where it does not fit, prefills run in the step's rows.
+constexpr int PREFILL_ROWS = 2560;
+
 extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32_t max_ctx, int32_t max_gamma,
                                sd_engine* out)
 {
@@ -245,7 +254,8 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     e->max_slots = max_slots;
     e->max_ctx = max_ctx;
     e->max_gamma = max_gamma;
-    e->rows_max = max_slots * (max_gamma + 1);
+    const int step_rows = max_slots * (max_gamma + 1);
+    e->rows_max = step_rows > PREFILL_ROWS ? step_rows : PREFILL_ROWS;
     e->f32 = cfg->dtype == SD_DTYPE_F32;
     e->w.assign(sd_num_weights(cfg), nullptr);
     e->qw.assign(4 * cfg->n_layers, nullptr);
@@ -254,32 +264,41 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     if (hipGetDevice(&e->dev) != hipSuccess) { delete e; return fail(SD_E_HIP, "hipGetDevice failed"); }
 
     const sd_model_cfg& c = *cfg;
-    size_t R = (size_t)e->rows_max;
     int qkvN = (c.n_q + 2 * c.n_kv) * c.head_dim, qd = c.n_q * c.head_dim;
-    struct { void** p; size_t bytes; } allocs[] = {
-        {(void**)&e->h, R * c.hidden * 4},
-        {(void**)&e->a, R * c.hidden * 4},
-        {(void**)&e->qkv, R * qkvN * 4},
-        {(void**)&e->qrot, R * qd * 4},
-        {(void**)&e->att, R * qd * 4},
-        {(void**)&e->gu, R * 2 * (size_t)c.ffn * 4},
-        {(void**)&e->act, R * c.ffn * 4},
-        {(void**)&e->att_part, attention_part_floats((int)R, c.n_q, c.n_kv, c.head_dim, e->f32) * 4},
-        {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
-        {(void**)&e->samp_part, sample_part_floats((int)R, c.vocab) * 4},
-        {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
-        {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
-        {(void**)&e->err, ERR_COUNT * 4},
-        {(void**)&e->pf_lim, (size_t)max_slots * 4},
-        {(void**)&e->gpart, gpart_bytes(c, e->rows_max)},
-    };
-    e->gpart_cap = gpart_bytes(c, e->rows_max) / 4;
-    for (auto& al : allocs) {
-        if (hipMalloc(al.p, al.bytes) != hipSuccess) {
-            free_ws(e);
-            delete e;
+    for (bool fits = false; !fits;) {
+        const size_t R = (size_t)e->rows_max;
+        e->gpart_cap = gpart_bytes(c, e->rows_max) / 4;
+        struct { void** p; size_t bytes; } allocs[] = {
+            {(void**)&e->h, R * c.hidden * 4},
+            {(void**)&e->a, R * c.hidden * 4},
+            {(void**)&e->qkv, R * qkvN * 4},
+            {(void**)&e->qrot, R * qd * 4},
+            {(void**)&e->att, R * qd * 4},
+            {(void**)&e->gu, R * 2 * (size_t)c.ffn * 4},
+            {(void**)&e->act, R * c.ffn * 4},
+            {(void**)&e->att_part, attention_part_floats((int)R, c.n_q, c.n_kv, c.head_dim, e->f32) * 4},
+            {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
+            {(void**)&e->samp_part, sample_part_floats(step_rows, c.vocab) * 4},
+            {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
+            {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
+            {(void**)&e->err, ERR_COUNT * 4},
+            {(void**)&e->pf_lim, ((size_t)2 * max_slots + 1) * 4},
+            {(void**)&e->gpart, e->gpart_cap * 4},
+        };
+        fits = true;
+        for (auto& al : allocs) {
+            if (hipMalloc(al.p, al.bytes) == hipSuccess) continue;
             (void)hipGetLastError();
-            return fail(SD_E_NOMEM, "workspace allocation of %zu bytes failed", al.bytes);
+            *al.p = nullptr;
+            free_ws(e);
+            for (auto& done : allocs) *done.p = nullptr;
+            if (e->rows_max == step_rows) {
+                delete e;
+                return fail(SD_E_NOMEM, "workspace allocation of %zu bytes failed", al.bytes);
+            }
+            e->rows_max = step_rows;
+            fits = false;
+            break;
         }
     }
     // RoPE table: cos/sin(pos * theta^(-2i/d)) computed in double on the host
@@ -421,7 +440,7 @@ static act_t act_of(sd_engine e, bool draft) { return e->f32 ? ACT_F32 : (draft 
 // Returns the K splits of a deferred split-K projection (partials in gpart),
 // or 1 when C holds the result.
 static int proj(sd_engine e, bool draft, int layer, int which, const void* A, float* C, int M, int ldc, gemm_mode mode,
-                hipStream_t s)
+                hipStream_t s, const int32_t* live)
 {
     int N, K;
     prj_shape(e->c, which, &N, &K);
@@ -439,12 +458,13 @@ static int proj(sd_engine e, bool draft, int layer, int which, const void* A, fl
     const void* w = W(e, layer, widx[which]);
     if (e->f32) { launch_gemm_f32((const float*)A, (const float*)w, C, M, N, K, ldc, mode, s); return 1; }
     return launch_gemm_bf16((const uint16_t*)A, (const uint16_t*)w, C, e->gpart, e->gpart_cap, M, N, K, ldc, mode, true, s,
-                            !e->no_dma);
+                            !e->no_dma, live);
 }
 
 // The gate/up projection with SwiGLU in its epilogue, writing act directly;
 // false when the shape has no fused kernel (or fusion is switched off).
-static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void* act, act_t at, int M, hipStream_t s)
+static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void* act, act_t at, int M, hipStream_t s,
+                        const int32_t* live)
 {
     if (e->f32 || e->no_fuse) return false;
     const sd_model_cfg& c = e->c;
@@ -454,20 +474,26 @@ static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void*
                                      c.hidden, s) != 0;
     }
     return launch_gemm_bf16_swiglu((const uint16_t*)A, (const uint16_t*)W(e, layer, 4), act, at, M, c.ffn, c.hidden,
-                                   s, !e->no_dma) != 0;
+                                   s, !e->no_dma, live) != 0;
 }
 
 // One forward pass over B sequences x n tokens (row r = b*n + i at position
 // kv_len + off + i).  Token of row (b, i): i == 0 ? tokA[b*sA] :
 // tokB[b*sB + i - 1].  If logits != NULL, row r's logits go to logits + r*ldl;
 // otherwise the last layer's FFN (which only feeds the logits) is skipped.
+// packed: the rows of a ragged-prefill round (rows_t), set up by
+// launch_prefill_lim.
 static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const int32_t* tokA, int sA,
                     const int32_t* tokB, int sB, int n, int off, float* logits, long ldl, hipStream_t s,
-                    const int32_t* lim = nullptr)
+                    bool packed = false)
 {
     const sd_model_cfg& c = e->c;
     rows_t r = {B, n, off, slots, e->kv_len, e->max_slots, e->max_ctx, e->err};
-    r.lim = lim;
+    if (packed) {
+        r.lim = e->pf_lim;
+        r.row0 = e->pf_lim + e->max_slots;
+        r.live = e->pf_lim + 2 * e->max_slots;
+    }
     cache_t kv = {e->k, e->v, e->f32 ? 1 : 0, c.n_kv, c.head_dim, e->geo};
     const int R = B * n;
     const act_t at = act_of(e, draft);
@@ -479,7 +505,7 @@ static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const 
     { tscope t(e, T_MISC, s);
       launch_embed_rmsnorm(r, tokA, sA, tokB, sB, e->w[0], e->f32, c.hidden, c.vocab, e->h, W(e, 0, 0), c.rms_eps, e->a, at, plan, s); }
     for (int l = 0; l < c.n_layers; ++l) {
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_QKV, e->a, e->qkv, R, qkvN, GEMM_STORE, s); }
+        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_QKV, e->a, e->qkv, R, qkvN, GEMM_STORE, s, r.live); }
         if (!logits && l == c.n_layers - 1) {
             // the rest of the last layer only feeds the logits: the new K/V rows alone
             tscope t(e, T_MISC, s);
@@ -493,20 +519,20 @@ static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const 
             tscope t(e, T_MISC, s);
             launch_attention_combine(r, plan, c.n_q, c.n_kv, c.head_dim, e->att_part, e->att, at, s);
         }
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_O, e->att, e->h, R, c.hidden, GEMM_ADD, s); }
-        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, W(e, l, 3), e->f32, c.rms_eps, e->a, at, s); }
+        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_O, e->att, e->h, R, c.hidden, GEMM_ADD, s, r.live); }
+        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, W(e, l, 3), e->f32, c.rms_eps, e->a, at, r.live, s); }
         bool fused;
-        { tscope t(e, pcls, s); fused = proj_swiglu(e, draft, l, e->a, e->act, at, R, s); }
+        { tscope t(e, pcls, s); fused = proj_swiglu(e, draft, l, e->a, e->act, at, R, s, r.live); }
         if (!fused) {
-            { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_GU, e->a, e->gu, R, 2 * c.ffn, GEMM_STORE, s); }
-            { tscope t(e, T_MISC, s); launch_silu_mul(e->gu, e->gpart, S, R, c.ffn, e->act, at, s); }
+            { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_GU, e->a, e->gu, R, 2 * c.ffn, GEMM_STORE, s, r.live); }
+            { tscope t(e, T_MISC, s); launch_silu_mul(e->gu, e->gpart, S, R, c.ffn, e->act, at, r.live, s); }
         }
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_DOWN, e->act, e->h, R, c.hidden, GEMM_ADD, s); }
+        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_DOWN, e->act, e->h, R, c.hidden, GEMM_ADD, s, r.live); }
         // next layer's attention norm, or the final norm (the LM head stays in the target precision)
         const bool last = l == c.n_layers - 1;
         const act_t nt = last ? (e->f32 ? ACT_F32 : ACT_BF16) : at;
         const void* g = last ? e->w[1] : W(e, l + 1, 0);
-        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, g, e->f32, c.rms_eps, e->a, nt, s); }
+        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, g, e->f32, c.rms_eps, e->a, nt, r.live, s); }
     }
     if (logits) {
         tscope t(e, T_LMHEAD, s);
@@ -552,13 +578,14 @@ extern "C" sd_status sd_prefill_ragged(sd_engine e, int32_t B, const int32_t* sl
     if (!tokens || !len) return fail(SD_E_INVAL, "NULL tokens or len");
     if (ld < 1 || ld > e->max_ctx) return fail(SD_E_INVAL, "ld=%d outside [1, max_ctx=%d]", ld, e->max_ctx);
     hipStream_t s = (hipStream_t)stream;
-    // rounds of nc positions for the whole batch; row (b, i) of a round is
-    // padding once sequence b has no token left (i >= lim[b])
+    // rounds of up to nc positions of every sequence, the rows of those that
+    // still have tokens packed
     int chunk = e->rows_max / B;
     for (int t0 = 0; t0 < ld; t0 += chunk) {
         int nc = ld - t0 < chunk ? ld - t0 : chunk;
-        launch_prefill_lim(B, len, t0, nc, ld, e->pf_lim, e->err, s);
-        forward(e, false, B, slots, tokens + t0, ld, tokens + t0 + 1, ld, nc, 0, nullptr, 0, s, e->pf_lim);
+        launch_prefill_lim(B, len, t0, nc, ld, e->pf_lim, e->pf_lim + e->max_slots, e->pf_lim + 2 * e->max_slots,
+                           e->err, s);
+        forward(e, false, B, slots, tokens + t0, ld, tokens + t0 + 1, ld, nc, 0, nullptr, 0, s, true);
         launch_kv_advance(B, slots, e->pf_lim, 0, e->kv_len, e->max_slots, e->err, s);
     }
     return launched("sd_prefill_ragged");

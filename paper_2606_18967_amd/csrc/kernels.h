@@ -9,14 +9,19 @@ enum act_t : int { ACT_F32 = 0, ACT_BF16 = 1, ACT_F16 = 2 };
 inline size_t act_bytes(act_t a) { return a == ACT_F32 ? 4 : 2; }
 
 // Row geometry of one forward call: B sequences with n new tokens each; row
-// r = b*n + i sits at absolute position kv_len[slots[b]] + off + i.
+// r = b*n + i sits at absolute position kv_len[slots[b]] + off + i.  A ragged
+// prefill packs the rows of its sequences instead: sequence b has lim[b] <= n
+// rows, from row0[b] on, and *live rows in all; its launches are sized for B*n
+// rows, and what lies past *live is skipped.
 struct rows_t {
     int B, n, off;
     const int32_t* slots;   // device [B]
     const int32_t* kv_len;  // device [max_slots]
     int max_slots, max_ctx;
     uint32_t* err;          // device error words
-    const int32_t* lim = nullptr;   // device [B] or NULL: rows (b, i >= lim[b]) are padding, skipped silently
+    const int32_t* lim = nullptr;   // device [B], row0 [B] and live [1], or NULL (no packing)
+    const int32_t* row0 = nullptr;
+    const int32_t* live = nullptr;
 };
 
 // KV cache geometry.  The element offset of (slot, layer, KV head h,
@@ -45,10 +50,11 @@ struct cache_t {
 // made on the device from the sequences' actual lengths by the forward's first
 // kernel (launch_embed_rmsnorm) and read by every layer's attention: items of
 // about equal length, longest first.  An item is a chunk [p0, p1) of one
-// sequence's positions [0, ctx), ctx = basepos + n clipped to max_ctx; nch is
+// sequence's positions [0, ctx), ctx = basepos + nlive clipped to max_ctx; nch is
 // the sequence's number of chunks (they are consecutive items), 0 in items past
 // the last.  A sequence without a usable slot or position is one empty item.
-struct att_item { int b, slot, basepos, ctx, p0, p1, nch, nlive; };
+// Its rows are row0 .. row0 + nlive - 1.
+struct att_item { int row0, slot, basepos, ctx, p0, p1, nch, nlive; };
 struct att_plan {
     int2* seq;             // device [B]: first item and number of items of each sequence
     att_item* item;        // device [max_items]
@@ -69,8 +75,9 @@ void attention_plan_bind(att_plan& p, void* buf, int max_slots);
 void launch_embed_rmsnorm(const rows_t& r, const int32_t* tokA, int sA, const int32_t* tokB, int sB,
                           const void* E, int w_f32, int H, int V, float* h, const void* gain, float eps,
                           void* out, act_t out_t, const att_plan& plan, hipStream_t s);
+// (live as rows_t::live)
 void launch_add_rmsnorm(float* h, const float* P, int S, int R, int H, const void* gain, int g_f32,
-                        float eps, void* out, act_t out_t, hipStream_t s);
+                        float eps, void* out, act_t out_t, const int32_t* live, hipStream_t s);
 void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, const float2* rope, int n_q,
                     const cache_t& c, int layer, float* q_out, hipStream_t s);
 // Attention in two launches: each item's softmax-weighted sums (the output
@@ -97,12 +104,15 @@ void launch_attention_combine(const rows_t& r, const att_plan& plan, int n_q, in
                               void* out, act_t out_t, hipStream_t s);
 // partial-result floats for any forward of up to R rows
 size_t attention_part_floats(int R, int n_q, int n_kv, int head_dim, int kv_f32);
-void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, hipStream_t s);
+void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, const int32_t* live,
+                     hipStream_t s);
 void launch_kv_advance(int B, const int32_t* slots, const int32_t* inc, int inc_const,
                        int32_t* kv_len, int max_slots, uint32_t* err, hipStream_t s);
-// lim[b] = clamp(len[b] - t0, 0, nc) for one round of a ragged prefill; a
-// length outside [0, ld] sets ERR_LEN and counts as 0
-void launch_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim, uint32_t* err, hipStream_t s);
+// One round of a ragged prefill: lim[b] = clamp(len[b] - t0, 0, nc), row0 their
+// prefix sums, live their sum; a length outside [0, ld] sets ERR_LEN and counts
+// as 0
+void launch_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim, int32_t* row0, int32_t* live,
+                        uint32_t* err, hipStream_t s);
 void launch_kv_poison(int B, const int32_t* slots, const int32_t* kv_len, int span,
                       const cache_t& c, int n_layers, int max_slots, int max_ctx, hipStream_t s);
 
@@ -114,16 +124,18 @@ enum gemm_mode : int { GEMM_STORE = 0, GEMM_ADD = 1 };
 // defer_reduce and S > 1 the partials are left in part ([S][M][N]) for the
 // consumer to sum; otherwise C holds the result.  lds_dma: 320-row tiles
 // without split-K use the DMA-fed kernel (same sums as the register-staged
-// one; false selects the latter).
+// one; false selects the latter).  live (device): row tiles past *live are
+// skipped (rows_t).
 int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part, size_t part_cap, int M, int N, int K,
-                     int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma = true);
+                     int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma = true,
+                     const int32_t* live = nullptr);
 // The gate/up projection with SwiGLU in its epilogue: out[M][F] (type out_t)
 // = SiLU(g) * u, [g | u] = A W^T with W [2F][K] (gate rows, then up rows).
 // Returns 1 when launched, 0 when the shape has no fused kernel (the caller
 // then runs the plain GEMM and launch_silu_mul).  The int4 form takes the
 // packed drafter layout of kernels_q4.hip.
 int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act_t out_t, int M, int F, int K,
-                            hipStream_t s, bool lds_dma = true);
+                            hipStream_t s, bool lds_dma = true, const int32_t* live = nullptr);
 int launch_gemm_q4_swiglu(const uint16_t* A, const uint32_t* Wq, const uint16_t* Sc, const uint8_t* Z, int fmt,
                           void* out, act_t out_t, int M, int F, int K, hipStream_t s);
 size_t gemm_part_floats(int M, int N, int K);

@@ -468,7 +468,8 @@ template <int MT, int WM, int WCN, int NST, bool SW>
 __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                             float* __restrict__ C, float* __restrict__ P, int M, int N,
                                                             int K, int ldc, int mode, int S, int mtiles, int total,
-                                                            void* __restrict__ out, int out_t)
+                                                            void* __restrict__ out, int out_t,
+                                                            const int32_t* __restrict__ live)
 {
     constexpr int BM = 32 * MT, BN = 64 * WCN, NWAVE = WM * WCN, RT = MT / WM;   // RT row blocks per wave
     constexpr int NA = BM / 8, NI = NA + BN / 8;               // 1 KB pieces (8 rows) per stage
@@ -487,6 +488,7 @@ __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __re
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wv / WCN, wn = wv % WCN;
     const int m0 = mt * BM, n0 = nt * BN;
+    if (live && m0 >= *live) return;                           // a row tile without a live row
     const int Ks = K / DBK / S, k0 = s * Ks;
     const int rows = min(M - m0, BM);
     const bool once = mtiles == 1;                             // no other m-tile reads these weights
@@ -781,6 +783,7 @@ struct dma_args {
     int M, N, K, ldc, mode;
     void* out;
     int out_t;
+    const int32_t* live;
 };
 
 template <int MT, int WM, int WCN, int NST, bool SW>
@@ -789,7 +792,7 @@ static void dma_go(const dma_args& a, int S, hipStream_t s)
     const int mtiles = (a.M + 32 * MT - 1) / (32 * MT);
     const int total = a.N / (64 * WCN) * mtiles * S;
     k_gemm_dma<MT, WM, WCN, NST, SW><<<dim3((total + 7) / 8 * 8), 64 * WM * WCN, 0, s>>>(
-        a.A, a.W, a.C, a.P, a.M, a.N, a.K, a.ldc, a.mode, S, mtiles, total, a.out, a.out_t);
+        a.A, a.W, a.C, a.P, a.M, a.N, a.K, a.ldc, a.mode, S, mtiles, total, a.out, a.out_t, a.live);
 }
 
 template <bool SW>
@@ -836,13 +839,13 @@ static void reduce_splits(const float* part, float* C, int M, int N, int ldc, in
 }
 
 int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part, size_t part_cap, int M, int N, int K,
-                     int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma)
+                     int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma, const int32_t* live)
 {
     if (use_dma(N, K)) {
         dma_tile p = dma_plan(M, N, K);
         if (p.S > 1 && (size_t)p.S * M * N > part_cap) p.S = 1;   // workspace too small: no split
         if (lds_dma || p.mt != 10) {
-            dma_launch<false>({A, W, C, part, M, N, K, ldc, mode, nullptr, 0}, p, s);
+            dma_launch<false>({A, W, C, part, M, N, K, ldc, mode, nullptr, 0, live}, p, s);
         } else {
             const int mtiles = (M + 319) / 320, total = N / TBN * mtiles * p.S;
             k_gemm_t32<10, false><<<dim3((total + 7) / 8 * 8), 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, p.S, mtiles,
@@ -871,7 +874,7 @@ int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part
 }
 
 int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act_t out_t, int M, int F, int K,
-                            hipStream_t s, bool lds_dma)
+                            hipStream_t s, bool lds_dma, const int32_t* live)
 {
     const int N = 2 * F;
     if (!use_dma(N, K) || F % 64) return 0;
@@ -880,7 +883,7 @@ int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act
     const dma_tile p = dma_plan(M, N, K);
     if (p.S != 1 || F % (32 * p.wcn)) return 0;
     if (lds_dma || p.mt != 10) {
-        dma_launch<true>({A, W, nullptr, nullptr, M, N, K, 0, 0, out, (int)out_t}, p, s);
+        dma_launch<true>({A, W, nullptr, nullptr, M, N, K, 0, 0, out, (int)out_t, live}, p, s);
     } else {
         const int mtiles = (M + 319) / 320, total = F / 64 * mtiles;
         k_gemm_t32<10, true><<<dim3((total + 7) / 8 * 8), 256, 0, s>>>(A, W, nullptr, nullptr, M, N, K, 0, 0, 1, mtiles,

@@ -87,11 +87,11 @@ __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
     __shared__ int s_cnt[64], s_sum, s_top, s_items;
     const int tid = threadIdx.x, nt = blockDim.x;
     auto seq_of = [&](int b) {
-        att_item it = {b, r.slots[b], 0, 0, 0, 0, 1, 0};
+        att_item it = {r.row0 ? r.row0[b] : b * r.n, r.slots[b], 0, 0, 0, 0, 1, 0};
         it.nlive = r.lim ? min(r.n, max(r.lim[b], 0)) : r.n;
         if (it.slot >= 0 && it.slot < r.max_slots) {
             it.basepos = r.kv_len[it.slot] + r.off;
-            it.ctx = max(0, min(it.basepos + r.n, r.max_ctx));
+            it.ctx = max(0, min(it.basepos + it.nlive, r.max_ctx));
         }
         return it;
     };
@@ -180,10 +180,10 @@ __global__ void __launch_bounds__(1024) k_embed_rmsnorm(rows_t r, const int32_t*
         make_att_plan(r, plan);
         return;
     }
-    const int row = blockIdx.x;
-    const int b = row / r.n, i = row - b * r.n;
-    const bool pad = r.lim && i >= r.lim[b];            // a padding row: embedded as token 0, never cached
-    const int tok = pad ? 0 : (i == 0) ? tokA[(size_t)b * sA] : tokB[(size_t)b * sB + i - 1];
+    const int b = blockIdx.x / r.n, i = blockIdx.x - b * r.n;
+    if (r.lim && i >= r.lim[b]) return;
+    const int row = r.row0 ? r.row0[b] + i : (int)blockIdx.x;
+    const int tok = (i == 0) ? tokA[(size_t)b * sA] : tokB[(size_t)b * sB + i - 1];
     const bool ok = tok >= 0 && tok < V;
     if (!ok && threadIdx.x == 0) flag_error(r.err, ERR_TOKEN);
     const T* er = E + (size_t)(ok ? tok : 0) * H;
@@ -211,10 +211,11 @@ __global__ void __launch_bounds__(1024) k_embed_rmsnorm(rows_t r, const int32_t*
 // batch runs on few CUs and is bound by that latency, not by its bytes).
 template <typename G, typename O, int NPT>
 __global__ void __launch_bounds__(1024) k_add_rmsnorm(float* h, const float* P, int S, int R, int H, const G* gain,
-                                                     float eps, void* out)
+                                                     float eps, void* out, const int32_t* live)
 {
     __shared__ float red[16];
     const int row = blockIdx.x;
+    if (live && row >= *live) return;
     float* hr = h + (size_t)row * H;
     const size_t RH = (size_t)R * H;
     // a thread's float4s past the row end read the last one (in bounds) and are dropped
@@ -294,17 +295,17 @@ __global__ void __launch_bounds__(256) k_rope_kv(rows_t r, const float* qkv, con
                                                  int n_q, int n_kv, int d, T* kc, T* vc, kv_geom g, int layer,
                                                  float* q_out, int upw)
 {
-    const int row = blockIdx.x;
     int b, i, slot, pos;
-    const bool ok = row_geom(r, row, &b, &i, &slot, &pos);
+    const bool ok = row_geom(r, blockIdx.x, &b, &i, &slot, &pos);
+    if (r.lim && i >= r.lim[b]) return;
+    const int row = r.row0 ? r.row0[b] + i : (int)blockIdx.x;
     const int hd = d / 2, units = n_q + 2 * n_kv;
     const int u0 = blockIdx.y * upw, nu = min(upw, units - u0);
     const size_t RN = (size_t)r.B * r.n * units * d;
     const size_t base_idx = (size_t)row * units * d;
     float* qo = q_out + (size_t)row * n_q * d;
-    const bool pad = r.lim && (row % r.n) >= r.lim[row / r.n];   // padding rows are not cached
-    if (!ok || pad) {
-        if (!pad && threadIdx.x == 0 && blockIdx.y == 0) {
+    if (!ok) {
+        if (threadIdx.x == 0 && blockIdx.y == 0) {
             const bool bad_slot = slot < 0 || slot >= r.max_slots;
             flag_error(r.err, bad_slot ? ERR_SLOT : ERR_CTX);
         }
@@ -372,8 +373,8 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 
     const int item = blockIdx.y, kvh = blockIdx.x;
     const att_item it = plan.item[item];
-    if (it.nch == 0) return;
-    const int b = it.b, slot = it.slot, basepos = it.basepos, p0 = it.p0, p1 = it.p1;   // p0 == p1: flagged by k_rope_kv
+    if (it.nch == 0 || it.nlive == 0) return;
+    const int row0 = it.row0, slot = it.slot, basepos = it.basepos, p0 = it.p0, p1 = it.p1;   // p0 == p1: flagged by k_rope_kv
 
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int pg = lane / LPP;                 // position group within the wave
@@ -389,10 +390,11 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 #pragma unroll
         for (int rr = 0; rr < ATT_RG; ++rr) {
             int qr = rg0 + rr;
-            bool live = qr < QR;
-            int g = live ? qr / r.n : 0, i = live ? qr - g * r.n : 0;
+            int g = qr < QR ? qr / r.n : 0, i = qr < QR ? qr - g * r.n : 0;
+            bool live = qr < QR && i < it.nlive;
+            if (!live) i = 0;
             int hq = kvh * G + g;
-            const float* qp = q + ((size_t)(b * r.n + i) * n_q + hq) * D + dd;
+            const float* qp = q + ((size_t)(row0 + i) * n_q + hq) * D + dd;
 #pragma unroll
             for (int e = 0; e < 8; ++e) { qv[rr][e] = live ? qp[e] * scale : 0.f; o[rr][e] = 0.f; }
             m[rr] = -INFINITY; l[rr] = 0.f;
@@ -459,9 +461,10 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
                 }
             }
             int g = qr / r.n, i = qr - g * r.n;
+            if (i >= it.nlive) continue;
             int hq = kvh * G + g;
             if (it.nch == 1) {
-                out[((size_t)(b * r.n + i) * n_q + hq) * D + k] = ls > 0.f ? os / ls : 0.f;
+                out[((size_t)(row0 + i) * n_q + hq) * D + k] = ls > 0.f ? os / ls : 0.f;
                 continue;
             }
             float* pp = part + part_index(item, n_kv, kvh, QR, qr, D);
@@ -537,10 +540,12 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     // fields (and the buffer resources built from them) in scalar registers
     const att_item it = plan.item[item];
     if (it.nch == 0) return;
-    const int b = __builtin_amdgcn_readfirstlane(it.b), slot = __builtin_amdgcn_readfirstlane(it.slot);
+    const int row0 = __builtin_amdgcn_readfirstlane(it.row0), slot = __builtin_amdgcn_readfirstlane(it.slot);
     const int basepos = __builtin_amdgcn_readfirstlane(it.basepos), ctx = __builtin_amdgcn_readfirstlane(it.ctx);
     const int p0 = __builtin_amdgcn_readfirstlane(it.p0), p1 = __builtin_amdgcn_readfirstlane(it.p1);
-    const int nlive = __builtin_amdgcn_readfirstlane(it.nlive);   // rows (b, i >= nlive) are padding: neither cached nor flagged
+    const int nlive = __builtin_amdgcn_readfirstlane(it.nlive);   // the sequence's rows: i < nlive
+    // a slice of rows of one head that all lie past them (slice 0 does not, so the new K/V rows are written)
+    if (nlive < r.n && (nlive == 0 || ((z * 16 * MQ) % r.n >= nlive && (z * 16 * MQ) % r.n + 16 * MQ <= r.n))) return;
     // a live row's slot, or its position outside [0, max_ctx), is flagged once per sequence
     if (p0 == 0 && z == 0 && kvh == 0 && threadIdx.x == 0) {
         if (slot < 0 || slot >= r.max_slots) flag_error(r.err, ERR_SLOT);
@@ -552,7 +557,8 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
             const int qrow = z * 16 * MQ + idx / D, d = idx % D;
             if (qrow >= G * r.n) continue;
             const int g = qrow / r.n, i = qrow - g * r.n;
-            const size_t oi = ((size_t)(b * r.n + i) * n_q + kvh * G + g) * D + d;
+            if (i >= nlive) continue;
+            const size_t oi = ((size_t)(row0 + i) * n_q + kvh * G + g) * D + d;
             if (out_t == ACT_F16) store_act<_Float16>(out, oi, 0.f);
             else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, 0.f);
             else store_act<float>(out, oi, 0.f);
@@ -811,9 +817,9 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                 float4 lo = z4, hi = z4;
                 if (qrow < QR) {
                     const int g = qrow / r.n, i = qrow - g * r.n, pos = basepos + i;
-                    // rows k_rope_kv does not rotate (padding, outside [0, max_ctx)) keep q = 0, as it writes
+                    // rows k_rope_kv does not rotate (past the sequence's, outside [0, max_ctx)) keep q = 0
                     if (i < nlive && pos >= 0 && pos < r.max_ctx) {
-                        const size_t ci = ((size_t)(b * r.n + i) * units + kvh * G + g) * D + 4 * gq;
+                        const size_t ci = ((size_t)(row0 + i) * units + kvh * G + g) * D + 4 * gq;
                         float4 a, c;
                         sum4x2(ci, a, c);
                         rot4(a, c, qs.rope + (size_t)pos * (D / 2) + 4 * gq, qscale, lo, hi);
@@ -825,13 +831,13 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                 const int tt = t - nlq, j = tt / (2 * QG), rem = tt - j * (2 * QG);
                 const bool isv = rem >= QG;
                 const int gq = isv ? rem - QG : rem, i = n0 - basepos + j, pos = basepos + i;
-                if (i >= nlive) continue;                       // padding rows are not cached
+                if (i >= nlive) continue;                       // past the sequence's rows
                 const long long pg = kv_page(kg, slot, pos / kg.P);
                 if (pg < 0) {
                     if (gq == 0) flag_error(r.err, ERR_PAGE);
                     continue;
                 }
-                const size_t ci = ((size_t)(b * r.n + i) * units + n_q + (isv ? n_kv : 0) + kvh) * D + 4 * gq;
+                const size_t ci = ((size_t)(row0 + i) * units + n_q + (isv ? n_kv : 0) + kvh) * D + 4 * gq;
                 float4 lo, hi;
                 sum4x2(ci, lo, hi);
                 if (!isv) rot4(lo, hi, qs.rope + (size_t)pos * (D / 2) + 4 * gq, 1.f, lo, hi);
@@ -923,10 +929,11 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
                 }
             }
             const int g = qrow / r.n, i = qrow - g * r.n;
+            if (i >= nlive) continue;
             if (it.nch == 1) {
                 // the sequence's only item: the normalized output directly (what
                 // k_attn_combine computes from one chunk)
-                const size_t oi = ((size_t)(b * r.n + i) * n_q + kvh * G + g) * D + d;
+                const size_t oi = ((size_t)(row0 + i) * n_q + kvh * G + g) * D + d;
                 const float v = ls > 0.f ? os / ls : 0.f;
                 if (out_t == ACT_F16) store_act<_Float16>(out, oi, v);
                 else if (out_t == ACT_BF16) store_act<uint16_t>(out, oi, v);
@@ -943,8 +950,10 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
 template <typename O>
 __global__ void k_attn_combine(rows_t r, att_plan plan, int n_q, int n_kv, int D, const float* part, void* out)
 {
-    const int row = blockIdx.x / n_q, hq = blockIdx.x - row * n_q;
-    const int b = row / r.n, i = row - b * r.n;
+    const int idx = blockIdx.x / n_q, hq = blockIdx.x - idx * n_q;
+    const int b = idx / r.n, i = idx - b * r.n;
+    if (r.lim && i >= r.lim[b]) return;
+    const int row = r.row0 ? r.row0[b] + i : idx;
     const int2 sq = plan.seq[b];
     const int nch = sq.y;
     if (nch <= 1) return;                               // the attention wrote the output
@@ -993,9 +1002,11 @@ __global__ void k_attn_combine(rows_t r, att_plan plan, int n_q, int n_kv, int D
 // ------------------------------------------------------------------ swiglu
 // out[row][f] = SiLU(g) * u with (g, u) = gu[row][f], gu[row][F + f]
 template <typename O>
-__global__ void __launch_bounds__(256) k_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out)
+__global__ void __launch_bounds__(256) k_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out,
+                                                  const int32_t* live)
 {
     const int row = blockIdx.x;
+    if (live && row >= *live) return;
     const int f = (blockIdx.y * 256 + threadIdx.x) * 4;
     if (f >= F) return;
     const size_t RN = (size_t)R * 2 * F;
@@ -1026,16 +1037,38 @@ __global__ void k_kv_advance(int B, const int32_t* slots, const int32_t* inc, in
     kv_len[s] += inc ? inc[b] : inc_const;
 }
 
-__global__ void k_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim, uint32_t* err)
+// one work-group; thread t takes the sequences t, t + 256, ... of each pass
+__global__ void __launch_bounds__(256) k_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim,
+                                                     int32_t* row0, int32_t* live, uint32_t* err)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    int n = len[b];
-    if (n < 0 || n > ld) {
-        flag_error(err, ERR_LEN);
-        n = 0;
+    __shared__ int wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int base = 0;
+    for (int b0 = 0; b0 < B; b0 += 256) {
+        const int b = b0 + tid;
+        int n = b < B ? len[b] : 0;
+        if (n < 0 || n > ld) {
+            flag_error(err, ERR_LEN);
+            n = 0;
+        }
+        n = min(max(n - t0, 0), nc);
+        int upto = n;                                       // inclusive sum over the wave
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(upto, o, WAVE);
+            if (lane >= o) upto += v;
+        }
+        __syncthreads();
+        if (lane == 63) wsum[wv] = upto;
+        __syncthreads();
+        int before = base;
+        for (int w = 0; w < wv; ++w) before += wsum[w];
+        if (b < B) {
+            lim[b] = n;
+            row0[b] = before + upto - n;
+        }
+        base += wsum[0] + wsum[1] + wsum[2] + wsum[3];
     }
-    lim[b] = min(max(n - t0, 0), nc);
+    if (tid == 0) *live = base;
 }
 
 template <typename T>
@@ -1087,31 +1120,31 @@ void launch_embed_rmsnorm(const rows_t& r, const int32_t* tokA, int sA, const in
 
 template <typename G, int NPT>
 static void add_rmsnorm_n(float* h, const float* P, int S, int R, int H, const G* g, float eps, void* out, act_t t,
-                          hipStream_t s)
+                          const int32_t* live, hipStream_t s)
 {
     const int th = ((H / 4 + NPT - 1) / NPT + 63) & ~63;      // <= 1024 by the caller's choice of NPT
-    if (t == ACT_F32) k_add_rmsnorm<G, float, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out);
-    else if (t == ACT_BF16) k_add_rmsnorm<G, uint16_t, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out);
-    else k_add_rmsnorm<G, _Float16, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out);
+    if (t == ACT_F32) k_add_rmsnorm<G, float, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out, live);
+    else if (t == ACT_BF16) k_add_rmsnorm<G, uint16_t, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out, live);
+    else k_add_rmsnorm<G, _Float16, NPT><<<R, th, 0, s>>>(h, P, S, R, H, g, eps, out, live);
 }
 
 // the fewest float4s per thread that cover the row with at most 1024 threads
 // (hidden <= 32768, which the engine's configuration check guarantees)
 template <typename G>
 static void add_rmsnorm_t(float* h, const float* P, int S, int R, int H, const G* g, float eps, void* out, act_t t,
-                          hipStream_t s)
+                          const int32_t* live, hipStream_t s)
 {
-    if (H <= 4 * 1024) add_rmsnorm_n<G, 1>(h, P, S, R, H, g, eps, out, t, s);
-    else if (H <= 8 * 1024) add_rmsnorm_n<G, 2>(h, P, S, R, H, g, eps, out, t, s);
-    else if (H <= 16 * 1024) add_rmsnorm_n<G, 4>(h, P, S, R, H, g, eps, out, t, s);
-    else add_rmsnorm_n<G, 8>(h, P, S, R, H, g, eps, out, t, s);
+    if (H <= 4 * 1024) add_rmsnorm_n<G, 1>(h, P, S, R, H, g, eps, out, t, live, s);
+    else if (H <= 8 * 1024) add_rmsnorm_n<G, 2>(h, P, S, R, H, g, eps, out, t, live, s);
+    else if (H <= 16 * 1024) add_rmsnorm_n<G, 4>(h, P, S, R, H, g, eps, out, t, live, s);
+    else add_rmsnorm_n<G, 8>(h, P, S, R, H, g, eps, out, t, live, s);
 }
 
 void launch_add_rmsnorm(float* h, const float* P, int S, int R, int H, const void* gain, int g_f32, float eps,
-                        void* out, act_t out_t, hipStream_t s)
+                        void* out, act_t out_t, const int32_t* live, hipStream_t s)
 {
-    if (g_f32) add_rmsnorm_t(h, P, S, R, H, (const float*)gain, eps, out, out_t, s);
-    else add_rmsnorm_t(h, P, S, R, H, (const uint16_t*)gain, eps, out, out_t, s);
+    if (g_f32) add_rmsnorm_t(h, P, S, R, H, (const float*)gain, eps, out, out_t, live, s);
+    else add_rmsnorm_t(h, P, S, R, H, (const uint16_t*)gain, eps, out, out_t, live, s);
 }
 
 void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, const float2* rope, int n_q,
@@ -1133,13 +1166,14 @@ att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32
     att_plan p = {};
     const int QR = n_q / n_kv * n;
     p.mq = QR > 48 ? 4 : (QR + 15) / 16;
-    p.zs = kv_f32 ? 1 : (QR + 16 * p.mq - 1) / (16 * p.mq);
+    p.zs = (QR + 16 * p.mq - 1) / (16 * p.mq);
     p.min_chunk = kv_f32 ? ATT_CH : ATT_MIN_CHUNK;
     p.target = ATT_TARGET_WGS / (n_kv * p.zs);
     if (p.target < 1) p.target = 1;
     const long long cap = (long long)B * ((max_ctx + p.min_chunk - 1) / p.min_chunk);   // chunks the cache has room for
     p.max_items = B >= p.target ? B : (cap < p.target ? (int)cap : p.target);
     p.whole = p.max_items == B;
+    if (kv_f32) p.zs = 1;                                  // one work-group takes all of a KV head's query rows
     return p;
 }
 
@@ -1226,12 +1260,13 @@ void launch_attention_combine(const rows_t& r, const att_plan& plan, int n_q, in
     else k_attn_combine<_Float16><<<R * n_q, D, 0, s>>>(r, plan, n_q, n_kv, D, part, out);
 }
 
-void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, hipStream_t s)
+void launch_silu_mul(const float* gu, const float* P, int S, int R, int F, void* out, act_t out_t, const int32_t* live,
+                     hipStream_t s)
 {
     dim3 grid(R, (F / 4 + 255) / 256);
-    if (out_t == ACT_F32) k_silu_mul<float><<<grid, 256, 0, s>>>(gu, P, S, R, F, out);
-    else if (out_t == ACT_BF16) k_silu_mul<uint16_t><<<grid, 256, 0, s>>>(gu, P, S, R, F, out);
-    else k_silu_mul<_Float16><<<grid, 256, 0, s>>>(gu, P, S, R, F, out);
+    if (out_t == ACT_F32) k_silu_mul<float><<<grid, 256, 0, s>>>(gu, P, S, R, F, out, live);
+    else if (out_t == ACT_BF16) k_silu_mul<uint16_t><<<grid, 256, 0, s>>>(gu, P, S, R, F, out, live);
+    else k_silu_mul<_Float16><<<grid, 256, 0, s>>>(gu, P, S, R, F, out, live);
 }
 
 void launch_kv_advance(int B, const int32_t* slots, const int32_t* inc, int inc_const, int32_t* kv_len,
@@ -1240,9 +1275,10 @@ void launch_kv_advance(int B, const int32_t* slots, const int32_t* inc, int inc_
     k_kv_advance<<<(B + 255) / 256, 256, 0, s>>>(B, slots, inc, inc_const, kv_len, max_slots, err);
 }
 
-void launch_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim, uint32_t* err, hipStream_t s)
+void launch_prefill_lim(int B, const int32_t* len, int t0, int nc, int ld, int32_t* lim, int32_t* row0, int32_t* live,
+                        uint32_t* err, hipStream_t s)
 {
-    k_prefill_lim<<<(B + 255) / 256, 256, 0, s>>>(B, len, t0, nc, ld, lim, err);
+    k_prefill_lim<<<1, 256, 0, s>>>(B, len, t0, nc, ld, lim, row0, live, err);
 }
 
 void launch_kv_poison(int B, const int32_t* slots, const int32_t* kv_len, int span, const cache_t& c,
