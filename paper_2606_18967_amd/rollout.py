@@ -256,7 +256,7 @@ class Rollout:
             graph = torch.cuda.CUDAGraph()
             side = torch.cuda.Stream(device=self.dev)          # default priority
             side.wait_stream(torch.cuda.current_stream())
-            with torch.cuda.graph(graph, stream=side):
+            with sdrl.no_collection(), torch.cuda.graph(graph, stream=side):
                 eager()
             torch.cuda.current_stream().wait_stream(side)
             torch.cuda.synchronize()

@@ -11,7 +11,9 @@ The library must have been built (``paper_2606_18967_amd/build.py`` or
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
+import gc
 import os
 
 import torch
@@ -359,6 +361,20 @@ def sd_step(eng: Engine, bufs: SDBuffers, slots, last_tok, T, seed, step):
     eng.rollback(slots, bufs.n_emit)
 
 
+@contextlib.contextmanager
+def no_collection():
+    """Keeps Python's garbage collector out of a graph capture: an engine or
+    graph left in a reference cycle would be destroyed inside it, and the frees
+    and device synchronisation of its destructor invalidate the capture."""
+    collecting = gc.isenabled()
+    gc.disable()
+    try:
+        yield
+    finally:
+        if collecting:
+            gc.enable()
+
+
 class StepGraph:
     """One SD step for a fixed batch (slots, last_tok, buffers, gamma, T and
     the Philox key), captured once as a HIP graph through torch: draft,
@@ -374,7 +390,7 @@ class StepGraph:
         self.graph = torch.cuda.CUDAGraph()
         side = torch.cuda.Stream(device=eng.device)            # default priority
         side.wait_stream(torch.cuda.current_stream())
-        with torch.cuda.graph(self.graph, stream=side):
+        with no_collection(), torch.cuda.graph(self.graph, stream=side):
             sd_step(eng, bufs, slots, last_tok, T, seed, step)
             torch.add(bufs.next_tok, 0, out=last_tok)             # a kernel node, not a copy node
         torch.cuda.current_stream().wait_stream(side)
