@@ -747,6 +747,14 @@ static bool use_dma(int N, int K) { return N % 128 == 0 && K % DBK == 0 && K >= 
 // 283 us), narrow ones elsewhere (8B gate/up at M = 128: 58 against 71; down
 // projections with half the splits).  Heights of 96 and 160 rows are built at
 // 256 columns only (LM head at M = 148: 214 us, in a 192-row tile 241).
+// The narrow 64-row tile with a ring of three stages fits a CU twice: unsplit
+// launches of 257 to 512 of them run at once, a stage of both in 1.62 times a
+// stage of one (32B gate/up at 28 rows: 90 us, 98 in 216 wide tiles).
+static bool dma_two_per_cu(int mt, int wcn, int S, long long tiles)
+{
+    return mt == 2 && wcn == 2 && S == 1 && tiles > 256 && tiles <= 512;
+}
+
 static dma_tile dma_plan(int M, int N, int K)
 {
     const int KB = K / DBK;
@@ -760,7 +768,8 @@ static dma_tile dma_plan(int M, int N, int K)
         const double stage = (.42 + .125 * mt) * (wcn == 4 ? 1.65 : 1.);
         for (int S = 1; S <= DMA_MAX_SPLIT && 2 * S <= KB; ++S) {
             if (KB % S) continue;
-            const double wgs = (double)tiles * S, rounds = wgs <= 256 ? 1. : wgs / 256 + .35;
+            const double wgs = (double)tiles * S;
+            const double rounds = wgs <= 256 ? 1. : dma_two_per_cu(mt, wcn, S, tiles) ? 1.62 : wgs / 256 + .35;
             const double t = rounds * (KB / S + 3) * stage + (S > 1 ? 8 + 8e-6 / 5 * S * M * N : 0.);
             if (!best.mt || t < least) best = {mt, wcn, S}, least = t;
         }
@@ -810,7 +819,10 @@ static void dma_launch(const dma_args& a, dma_tile p, hipStream_t s)
         }
     } else {
         switch (p.mt) {
-            case 2: dma_go<2, 2, 2, 5, SW>(a, p.S, s); break;
+            case 2:
+                if (dma_two_per_cu(2, 2, p.S, (long long)(a.N / 128) * ((a.M + 63) / 64))) dma_go<2, 2, 2, 3, SW>(a, p.S, s);
+                else dma_go<2, 2, 2, 5, SW>(a, p.S, s);
+                break;
             case 4: dma_go<4, 2, 2, 5, SW>(a, p.S, s); break;
             case 6: dma_go<6, 2, 2, 3, SW>(a, p.S, s); break;
             case 8: dma_go<8, 2, 2, 3, SW>(a, p.S, s); break;

@@ -102,3 +102,10 @@ def test_more_sequences_than_items_with_an_empty_and_an_unusable_one(page):
     slots[11] = -1
     say("more sequences than items", page, max(lens))
     verify_against_oracle(lens, 640, 2, page, slots, check=[0, 5, 10, 12, 40, 68, 69])
+
+
+@pytest.mark.parametrize("max_ctx", [512, 513], ids=["whole", "cut"])
+def test_caches_on_either_side_of_the_short_rule(max_ctx):
+    lens = [509, 0, 31, 257, 127, 128, 380]              # the longest fills the short cache
+    say("short cache", max_ctx)
+    verify_against_oracle(lens, max_ctx, 2, 0)
