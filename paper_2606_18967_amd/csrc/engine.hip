@@ -205,12 +205,14 @@ extern "C" size_t sd_drafter_bytes_fmt(const sd_model_cfg* c, int32_t fmt)
 
 extern "C" size_t sd_drafter_bytes(const sd_model_cfg* c) { return sd_drafter_bytes_fmt(c, SD_DRAFT_W4); }
 
-// Largest split-K scratch any projection or the LM head needs for up to R rows.
-static size_t gpart_bytes(const sd_model_cfg& c, int R)
+// Largest split-K scratch any projection or the LM head needs for up to R rows:
+// of every row count of a step, and of every 16th of a longer prefill's (where
+// the scratch falls short, that projection runs unsplit).
+static size_t gpart_bytes(const sd_model_cfg& c, int step_rows, int R)
 {
     if (c.dtype == SD_DTYPE_F32) return 256;
     size_t mx = 0;
-    for (int m = 1; m <= R; ++m) {
+    for (int m = 1; m <= R; m += m < step_rows ? 1 : 16) {
         size_t f = gemm_part_floats(m, c.vocab, c.hidden);
         mx = f > mx ? f : mx;
         for (int w = 0; w < 4; ++w) {
@@ -267,7 +269,7 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     int qkvN = (c.n_q + 2 * c.n_kv) * c.head_dim, qd = c.n_q * c.head_dim;
     for (bool fits = false; !fits;) {
         const size_t R = (size_t)e->rows_max;
-        e->gpart_cap = gpart_bytes(c, e->rows_max) / 4;
+        e->gpart_cap = gpart_bytes(c, step_rows, e->rows_max) / 4;
         struct { void** p; size_t bytes; } allocs[] = {
             {(void**)&e->h, R * c.hidden * 4},
             {(void**)&e->a, R * c.hidden * 4},
