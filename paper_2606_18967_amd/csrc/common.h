@@ -58,17 +58,8 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// SiLU(g) u = g u / (1 + e^-g).  The quotient by v_rcp_f32 and one Newton step
-// (within an ulp, as the division; d = inf gives 0): the correctly rounded
-// division is about ten instructions, 80 of them per lane in the 320-row
-// tiles' epilogue.
-__device__ __forceinline__ float swiglu(float g, float u)
-{
-    const float d = 1.f + __expf(-g);
-    float r = __builtin_amdgcn_rcpf(d);
-    r = d < 3.0e38f ? __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r) : r;
-    return g * r * u;
-}
+// SiLU(g) u = g / (1 + e^-g) u, the quotient correctly rounded
+__device__ __forceinline__ float swiglu(float g, float u) { return g / (1.f + __expf(-g)) * u; }
 
 // ------------------------------------------------------------ reductions
 __device__ __forceinline__ float wave_sum(float v)
