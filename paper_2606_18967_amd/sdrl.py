@@ -15,6 +15,7 @@ import contextlib
 import ctypes as C
 import gc
 import os
+import threading
 
 import torch
 
@@ -361,18 +362,29 @@ def sd_step(eng: Engine, bufs: SDBuffers, slots, last_tok, T, seed, step):
     eng.rollback(slots, bufs.n_emit)
 
 
+_capture_lock = threading.Lock()
+_captures = [0, False]                 # captures running, whether the collector was on before the first
+
+
 @contextlib.contextmanager
 def no_collection():
     """Keeps Python's garbage collector out of a graph capture: an engine or
     graph left in a reference cycle would be destroyed inside it, and the frees
-    and device synchronisation of its destructor invalidate the capture."""
-    collecting = gc.isenabled()
-    gc.disable()
+    and device synchronisation of its destructor invalidate the capture.  The
+    collector is the whole process's, so captures of several threads share its
+    rest: it is off from the first one's start to the last one's end."""
+    with _capture_lock:
+        if not _captures[0]:
+            _captures[1] = gc.isenabled()
+        _captures[0] += 1
+        gc.disable()
     try:
         yield
     finally:
-        if collecting:
-            gc.enable()
+        with _capture_lock:
+            _captures[0] -= 1
+            if not _captures[0] and _captures[1]:
+                gc.enable()
 
 
 class StepGraph:

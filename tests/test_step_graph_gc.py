@@ -1,8 +1,9 @@
 """Capturing a step graph keeps Python's garbage collector out of the capture
-(an engine or graph in a reference cycle would be destroyed inside it), and
-leaves the collector as it was."""
+(an engine or graph in a reference cycle would be destroyed inside it), also
+while another thread's capture ends, and leaves the collector as it was."""
 import contextlib
 import gc
+import threading
 import types
 
 import pytest
@@ -36,4 +37,31 @@ def test_no_collection_inside_the_capture(monkeypatch, enabled, fails):
                            0, 0)
         assert seen == [False] and gc.isenabled() == enabled
     finally:
+        (gc.enable if was else gc.disable)()
+
+
+@pytest.mark.parametrize("enabled", [True, False])
+def test_overlapping_captures_of_two_threads(enabled):
+    entered, left = threading.Event(), threading.Event()
+    was = gc.isenabled()
+    (gc.enable if enabled else gc.disable)()
+
+    def first():
+        with sdrl.no_collection():
+            entered.set()
+            assert second_in.wait(20)
+        left.set()
+
+    second_in = threading.Event()
+    t = threading.Thread(target=first)
+    try:
+        t.start()
+        assert entered.wait(20)
+        with sdrl.no_collection():
+            second_in.set()
+            assert left.wait(20)
+            assert not gc.isenabled()                # the first capture has ended, this one has not
+        assert gc.isenabled() == enabled
+    finally:
+        t.join()
         (gc.enable if was else gc.disable)()
