@@ -450,21 +450,31 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// The stage a tile starts its K range with (it goes round).  Rows are K
-// elements apart, so at one k all rows of all tiles lie in the same few memory
-// channels; tiles that walk K in step crowd them (8B gate/up at M = 64: 49 ->
-// 43 us; no difference at 128 rows and more).  The gate and the up
-// columns of a feature start alike, in the plain form and in the SwiGLU form
-// (whose tile takes half as many features), so that both sum in one order.
+// ROT: the stage a tile starts its K range with (it goes round).  The gate and
+// the up columns of a feature start alike, in the plain form and in the SwiGLU
+// form (whose tile takes half as many features), so that both sum in one order.
 __device__ __forceinline__ int dma_rot(int nt, int s, int tiles, int Ks, bool sw)
 {
     const int t = sw ? nt >> 1 : (tiles % 2 == 0 && nt >= tiles / 2 ? nt - tiles / 2 : nt);
     return tiles % 2 ? 0 : (t * 5 + s) % Ks;
 }
 
+// Where tiles rotate: rows are K elements apart, so with a K of a multiple of
+// 4096 all rows of all tiles lie at one k in the same few memory channels, and
+// tiles that walk K in step crowd them (8B gate/up at 2, 64 and 65 rows: 42, 46
+// and 52 us, rotated 38, 41 and 45).  With other K the first round of tiles does
+// better in step (32B gate/up at 2, 64 and 128 rows: 87, 93 and 108 us, rotated
+// 93, 100 and 114); launches of several rounds gain between 65 and 160 rows (32B
+// LM head at 96 and 128: 317 and 332 us, rotated 304 and 326; at 64 and 256
+// within 1%).  From 161 rows on it makes no difference.
+static bool dma_rotates(int mt, long long tiles, int K)
+{
+    return mt <= 5 && (K % 4096 == 0 || (mt >= 3 && tiles > 256));
+}
+
 __device__ __forceinline__ int dma_sw(int r) { return (r ^ (r >> 3)) & 7; }
 
-template <int MT, int WM, int WCN, int NST, bool SW>
+template <int MT, int WM, int WCN, int NST, bool SW, bool ROT>
 __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                             float* __restrict__ C, float* __restrict__ P, int M, int N,
                                                             int K, int ldc, int mode, int S, int mtiles, int total,
@@ -514,10 +524,10 @@ __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __re
             dst[q] = BM * DRB + (t - NA) * 1024;
         }
     }
-    const int rot = MT == 10 ? 0 : dma_rot(nt, s, N / BN, Ks, SW);
+    const int rot = ROT ? dma_rot(nt, s, N / BN, Ks, SW) : 0;
     auto issue = [&](int kb) {
         const uint32_t buf = sbase + (kb % NST) * STG;
-        const size_t at = (size_t)(kb + rot < Ks ? kb + rot : kb + rot - Ks) * DBK;
+        const size_t at = (size_t)(ROT && kb + rot >= Ks ? kb + rot - Ks : kb + rot) * DBK;
 #pragma unroll
         for (int q = 0; q < CNT; ++q) {
             if (wv + q * NWAVE >= NA && once) lds_dma16_nt(src[q] + at, buf + dst[q]);
@@ -747,14 +757,6 @@ static bool use_dma(int N, int K) { return N % 128 == 0 && K % DBK == 0 && K >= 
 // 283 us), narrow ones elsewhere (8B gate/up at M = 128: 58 against 71; down
 // projections with half the splits).  Heights of 96 and 160 rows are built at
 // 256 columns only (LM head at M = 148: 214 us, in a 192-row tile 241).
-// The narrow 64-row tile with a ring of three stages fits a CU twice: unsplit
-// launches of 257 to 512 of them run at once, a stage of both in 1.62 times a
-// stage of one (32B gate/up at 28 rows: 90 us, 98 in 216 wide tiles).
-static bool dma_two_per_cu(int mt, int wcn, int S, long long tiles)
-{
-    return mt == 2 && wcn == 2 && S == 1 && tiles > 256 && tiles <= 512;
-}
-
 static dma_tile dma_plan(int M, int N, int K)
 {
     const int KB = K / DBK;
@@ -768,8 +770,7 @@ static dma_tile dma_plan(int M, int N, int K)
         const double stage = (.42 + .125 * mt) * (wcn == 4 ? 1.65 : 1.);
         for (int S = 1; S <= DMA_MAX_SPLIT && 2 * S <= KB; ++S) {
             if (KB % S) continue;
-            const double wgs = (double)tiles * S;
-            const double rounds = wgs <= 256 ? 1. : dma_two_per_cu(mt, wcn, S, tiles) ? 1.62 : wgs / 256 + .35;
+            const double wgs = (double)tiles * S, rounds = wgs <= 256 ? 1. : wgs / 256 + .35;
             const double t = rounds * (KB / S + 3) * stage + (S > 1 ? 8 + 8e-6 / 5 * S * M * N : 0.);
             if (!best.mt || t < least) best = {mt, wcn, S}, least = t;
         }
@@ -800,8 +801,13 @@ static void dma_go(const dma_args& a, int S, hipStream_t s)
 {
     const int mtiles = (a.M + 32 * MT - 1) / (32 * MT);
     const int total = a.N / (64 * WCN) * mtiles * S;
-    k_gemm_dma<MT, WM, WCN, NST, SW><<<dim3((total + 7) / 8 * 8), 64 * WM * WCN, 0, s>>>(
-        a.A, a.W, a.C, a.P, a.M, a.N, a.K, a.ldc, a.mode, S, mtiles, total, a.out, a.out_t, a.live);
+    auto go = [&](auto kern) {
+        kern<<<dim3((total + 7) / 8 * 8), 64 * WM * WCN, 0, s>>>(a.A, a.W, a.C, a.P, a.M, a.N, a.K, a.ldc, a.mode, S, mtiles,
+                                                               total, a.out, a.out_t, a.live);
+    };
+    if constexpr (MT <= 5)
+        if (dma_rotates(MT, (long long)(a.N / (64 * WCN)) * mtiles, a.K)) return go(k_gemm_dma<MT, WM, WCN, NST, SW, true>);
+    go(k_gemm_dma<MT, WM, WCN, NST, SW, false>);
 }
 
 template <bool SW>
@@ -819,10 +825,7 @@ static void dma_launch(const dma_args& a, dma_tile p, hipStream_t s)
         }
     } else {
         switch (p.mt) {
-            case 2:
-                if (dma_two_per_cu(2, 2, p.S, (long long)(a.N / 128) * ((a.M + 63) / 64))) dma_go<2, 2, 2, 3, SW>(a, p.S, s);
-                else dma_go<2, 2, 2, 5, SW>(a, p.S, s);
-                break;
+            case 2: dma_go<2, 2, 2, 5, SW>(a, p.S, s); break;
             case 4: dma_go<4, 2, 2, 5, SW>(a, p.S, s); break;
             case 6: dma_go<6, 2, 2, 3, SW>(a, p.S, s); break;
             case 8: dma_go<8, 2, 2, 3, SW>(a, p.S, s); break;
