@@ -425,7 +425,8 @@ __global__ void __launch_bounds__(256) k_gemm_t32(const uint16_t* __restrict__ A
 // wn's two 32-column blocks are the gate rows and the up rows of the same 32
 // features, so SiLU(g) u is formed in registers (no split-K there).  With S
 // K splits the partial sums go to P[s][M][N] as in k_gemm_stream.
-// Weights read by one m-tile only are non-temporal.
+// The weights' loads are non-temporal, also where several m-tiles read them (8B
+// gate/up at 1280 rows 278 us against 286, LM head at 640 626 against 644).
 // What bounds it: the weights' stream up to about 200 rows, so the ring is as
 // deep as LDS allows (three stages of 160 x 256 are 156 KB); the matrix cores
 // and the wait for the next stage at 320 rows (two stages).
@@ -501,7 +502,6 @@ __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __re
     if (live && m0 >= *live) return;                           // a row tile without a live row
     const int Ks = K / DBK / S, k0 = s * Ks;
     const int rows = min(M - m0, BM);
-    const bool once = mtiles == 1;                             // no other m-tile reads these weights
 
     // this lane's source row and chunk for each of its pieces
     const uint16_t* src[CNT];
@@ -530,8 +530,8 @@ __global__ void __launch_bounds__(64 * WM * WCN) k_gemm_dma(const uint16_t* __re
         const size_t at = (size_t)(ROT && kb + rot >= Ks ? kb + rot - Ks : kb + rot) * DBK;
 #pragma unroll
         for (int q = 0; q < CNT; ++q) {
-            if (wv + q * NWAVE >= NA && once) lds_dma16_nt(src[q] + at, buf + dst[q]);
-            else lds_dma16(src[q] + at, buf + dst[q]);
+            if (wv + q * NWAVE < NA) lds_dma16(src[q] + at, buf + dst[q]);
+            else lds_dma16_nt(src[q] + at, buf + dst[q]);
         }
     };
 
@@ -747,16 +747,20 @@ static bool use_dma(int N, int K) { return N % 128 == 0 && K % DBK == 0 && K >= 
 // Height: the lowest of 64, 96, 128, 160, 192, 256 and 320 rows that holds M;
 // more rows take 320-row tiles (fewer passes over the weights at a higher rate
 // per pass: 8B gate/up at 640 rows 154 us, in 256-row tiles 236).  Width and
-// split: the least of rounds of 256 work-groups x (stages + 3 to start) x a
-// stage's time, plus, with splits, 8 us and the partial sums' write and read at
+// split: the least of rounds of 256 work-groups x (stages + a ring's to start) x
+// a stage's time, plus, with splits, 8 us and the partial sums' write and read at
 // 5 TB/s (an unsplit gate/up forms SwiGLU in its epilogue).
 // A stage of 128 columns takes about .42 + .125 mt us with all CUs at work
 // (measured .67, .9, 1.4 and 1.7 at mt 2, 4, 8 and 10), one of 256 columns
-// 1.65 times that: half as many activation bytes per weight, but half as many
-// work-groups, so wide tiles go to large N (LM head at M = 128: 195 against
-// 283 us), narrow ones elsewhere (8B gate/up at M = 128: 58 against 71; down
-// projections with half the splits).  Heights of 96 and 160 rows are built at
-// 256 columns only (LM head at M = 148: 214 us, in a 192-row tile 241).
+// 1.65 times that, 1.45 at 320 rows: half as many activation bytes per weight,
+// but half as many work-groups, so wide tiles go to large N (LM head at M = 128:
+// 195 against 283 us) and to the projections past 320 rows (32B QKV with the
+// read of its partials at M = 400 and 640: 69 and 77 us, narrow with half the
+// splits 76 and 81), narrow ones elsewhere (8B gate/up at M = 128: 58 against
+// 71; down projections with half the splits).  Heights of 96 and 160 rows are
+// built at 256 columns only (LM head at M = 148: 214 us, in a 192-row tile 241).
+// The times are estimates: past one round they are up to a third too long, for
+// every choice alike.
 static dma_tile dma_plan(int M, int N, int K)
 {
     const int KB = K / DBK;
@@ -767,11 +771,12 @@ static dma_tile dma_plan(int M, int N, int K)
         int mt = M <= 64 ? 2 : M > 256 ? 10 : M > 192 ? 8 : M > 160 ? 6 : (M + 31) / 32;
         if (wcn == 2 && mt % 2) ++mt;
         const long long tiles = (long long)(N / (64 * wcn)) * ((M + 32 * mt - 1) / (32 * mt));
-        const double stage = (.42 + .125 * mt) * (wcn == 4 ? 1.65 : 1.);
+        const double stage = (.42 + .125 * mt) * (wcn == 2 ? 1. : mt == 10 ? 1.45 : 1.65);
+        const int start = mt == 10 ? 2 : 3;
         for (int S = 1; S <= DMA_MAX_SPLIT && 2 * S <= KB; ++S) {
             if (KB % S) continue;
             const double wgs = (double)tiles * S, rounds = wgs <= 256 ? 1. : wgs / 256 + .35;
-            const double t = rounds * (KB / S + 3) * stage + (S > 1 ? 8 + 8e-6 / 5 * S * M * N : 0.);
+            const double t = rounds * (KB / S + start) * stage + (S > 1 ? 8 + 8e-6 / 5 * S * M * N : 0.);
             if (!best.mt || t < least) best = {mt, wcn, S}, least = t;
         }
     }
