@@ -49,18 +49,19 @@ struct cache_t {
 // How one forward's attention divides the cached context among work-groups,
 // made on the device from the sequences' actual lengths by the forward's first
 // kernel (launch_embed_rmsnorm) and read by every layer's attention: items of
-// about equal length, longest first.  An item is a chunk [p0, p1) of one
-// sequence's positions [0, ctx), ctx = basepos + nlive clipped to max_ctx; nch is
-// the sequence's number of chunks (they are consecutive items), 0 in items past
-// the last.  A sequence without a usable slot or position is one empty item.
-// Its rows are row0 .. row0 + nlive - 1.
+// about equal length, whole sequences that do not all fit at once longest first.
+// An item is a chunk [p0, p1) of one sequence's positions [0, ctx), ctx = basepos
+// + nlive clipped to max_ctx; nch is the sequence's number of chunks (they are
+// consecutive items), 0 in items past the last.  A sequence without a usable slot
+// or position is one empty item.  Its rows are row0 .. row0 + nlive - 1.
 struct att_item { int row0, slot, basepos, ctx, p0, p1, nch, nlive; };
 struct att_plan {
-    int2* seq;             // device [B]: first item and number of items of each sequence
+    int2* seq;             // device [B]: first item and number of items of each sequence (unless whole)
     att_item* item;        // device [max_items]
     int target, min_chunk; // items wanted (where there are fewer sequences), shortest chunk (a multiple of 32)
     int max_items;         // grid size: max(target, B), fewer where max_ctx allows no more
     bool whole;            // every sequence is one item: no combine
+    bool in_order;         // and the items are in the sequences' order
     int mq, zs;            // query tiles per work-group and query-row slices (bf16 cache)
 };
 // the launch geometry of B sequences x n rows (no device pointers)

@@ -69,23 +69,30 @@ template <> __device__ __forceinline__ float4 load4<uint16_t>(const uint16_t* p)
 // most `target` chunks: every item is then resident at once, and they are of
 // about equal length whatever the contexts are.  (Chunks cut by max_ctx instead
 // left 13 ragged sequences in a cache with room for 8192 positions 200
-// work-groups: 53 us per launch.)  More sequences than the target stay whole.
-// Items go longest first, so that the last ones to start are short.  Before and
-// after, 8B shape: 53.3 -> 34.7 us (13 sequences of 1500-4500), 22.1 -> 16.9 (4),
-// 14.6 -> 11.0 (one of 2048), verify of 16 x 8 rows 80.8 -> 60.4; in order of
-// length, 200 sequences of 512-1536: 181 -> 161.
+// work-groups: 53 us per launch.)  More sequences than the target stay whole;
+// where they do not all fit at once they go longest first, so that the last
+// ones to start are short.  Before and after, 8B shape: 53.3 -> 34.7 us (13
+// sequences of 1500-4500), 22.1 -> 16.9 (4), 14.6 -> 11.0 (one of 2048), verify
+// of 16 x 8 rows 80.8 -> 60.4; in order of length, 200 sequences of 512-1536:
+// 181 -> 161.
+// What bounds it: one chain of dependent loads, barriers and LDS round trips
+// that the forward's first kernel waits for, so nothing is added up through
+// one LDS address (which serializes a wave's lanes) and nothing is sorted that
+// is resident at once: the kernel takes 5.3, 5.6, 5.0 and 6.1 us with the plans
+// of 16, 28, 64 and 200 sequences (7.5, 8.1, 10.3 and 13.5 otherwise; 5.1 to 5.4
+// without a plan).
 #ifndef ATT_FULL_CHUNK
 #define ATT_FULL_CHUNK 512
 #endif
 constexpr int PLAN_UNIT = 32;       // chunk lengths are multiples of a wave's block
-constexpr int PLAN_SEQS = 512;      // sequences planned in LDS (more, always whole, keep their order)
+constexpr int PLAN_SEQS = 512;      // sequences planned in LDS (more are always whole and in order)
 
 __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
 {
     __shared__ att_item s_it[PLAN_SEQS];
     __shared__ int s_len[PLAN_SEQS], s_nch[PLAN_SEQS], s_first[PLAN_SEQS];
-    __shared__ int s_cnt[64], s_sum, s_top, s_items;
-    const int tid = threadIdx.x, nt = blockDim.x;
+    __shared__ int s_cnt[64], s_sum[16], s_top[16], s_items;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     auto seq_of = [&](int b) {
         att_item it = {r.row0 ? r.row0[b] : b * r.n, r.slots[b], 0, 0, 0, 0, 1, 0};
         it.nlive = r.lim ? min(r.n, max(r.lim[b], 0)) : r.n;
@@ -93,72 +100,102 @@ __device__ void make_att_plan(const rows_t& r, const att_plan& pl)
             it.basepos = r.kv_len[it.slot] + r.off;
             it.ctx = max(0, min(it.basepos + it.nlive, r.max_ctx));
         }
+        it.p1 = it.ctx;
         return it;
     };
-    if (r.B > PLAN_SEQS) {
-        for (int b = tid; b < r.B; b += nt) {
-            att_item it = seq_of(b);
-            it.p1 = it.ctx;
-            pl.item[b] = it;
-            pl.seq[b] = make_int2(b, 1);
-        }
+    if (pl.in_order) {
+        for (int b = tid; b < r.B; b += nt) pl.item[b] = seq_of(b);
         return;
     }
+    if (pl.whole) {
+        for (int b = tid; b < r.B; b += nt) {
+            const att_item it = seq_of(b);
+            s_it[b] = it;
+            s_len[b] = it.ctx;
+            s_first[b] = 0;
+        }
+        __syncthreads();
+        // a sequence's item: the number of longer ones (ties: of lower index)
+        const int parts = max(nt / r.B, 1);
+        for (int t = tid; t < r.B * parts; t += nt) {
+            const int b = t / parts, len = s_len[b];
+            int first = 0;
+#pragma unroll 8
+            for (int o = t - b * parts; o < r.B; o += parts) {
+                const int lo = s_len[o];
+                first += lo > len || (lo == len && o < b);
+            }
+            atomicAdd(&s_first[b], first);
+        }
+        __syncthreads();
+        for (int b = tid; b < r.B; b += nt) pl.item[s_first[b]] = s_it[b];
+        return;
+    }
+    // fewer sequences than items: at most PLAN_SEQS
     if (tid < 64) s_cnt[tid] = 0;
-    if (tid == 64) s_sum = s_top = s_items = 0;
-    __syncthreads();
+    int sum = 0, top = 0;
     for (int b = tid; b < r.B; b += nt) {
         const att_item it = seq_of(b);
         s_it[b] = it;
-        s_first[b] = 0;
-        atomicAdd(&s_sum, it.ctx);
-        atomicMax(&s_top, it.ctx);
+        sum += it.ctx;
+        top = max(top, it.ctx);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o, WAVE);
+        top = max(top, __shfl_xor(top, o, WAVE));
+    }
+    if (lane == 0) s_sum[wv] = sum, s_top[wv] = top;
     __syncthreads();
-    int ch = max((s_top + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, pl.min_chunk);
-    if (r.B < pl.max_items) {
-        // candidate k: between the even share and the longest context, denser near the share
-        // (with little context in all, a quarter of the target's work-groups: shorter chunks would be all prologue)
-        const int few = max(pl.target / 4, 1);
-        const int even = (s_sum + pl.target - 1) / pl.target, fewer = (s_sum + few - 1) / few;
-        const int share = max(max(even, min(fewer, ATT_FULL_CHUNK)), pl.min_chunk);
-        const int base = min((share + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, ch);
-        const int more = (ch - base) / PLAN_UNIT;
-        auto cand = [&](int k) { return base + (more * (k * k) + 63 * 63 - 1) / (63 * 63) * PLAN_UNIT; };
-        const int k = tid & 63, ck = cand(k);
-        int cnt = 0;
-        for (int b = tid >> 6; b < r.B; b += nt >> 6) cnt += max(1, (s_it[b].ctx + ck - 1) / ck);
-        atomicAdd(&s_cnt[k], cnt);
-        __syncthreads();
-        const uint64_t fits = __builtin_amdgcn_ballot_w64(s_cnt[k] <= min(pl.target, pl.max_items));
-        ch = cand(fits ? (int)__builtin_ctzll(fits) : 63);
+    const int used = min((r.B + 63) >> 6, nt >> 6);            // waves that hold sequences
+    for (int w = 0; w < used; ++w) {
+        sum = w ? sum + s_sum[w] : s_sum[0];
+        top = w ? max(top, s_top[w]) : s_top[0];
     }
-    for (int b = tid; b < r.B; b += nt) {
-        const int ctx = s_it[b].ctx, nch = max(1, (ctx + ch - 1) / ch);
-        s_nch[b] = nch;
-        s_len[b] = ((ctx + nch - 1) / nch + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT;   // <= ch: no chunk is empty
-        atomicAdd(&s_items, nch);
-    }
+    // candidate k: between the even share and the longest context, denser near the share
+    // (with little context in all, a quarter of the target's work-groups: shorter chunks would be all prologue)
+    const int few = max(pl.target / 4, 1);
+    const int even = (sum + pl.target - 1) / pl.target, fewer = (sum + few - 1) / few;
+    const int share = max(max(even, min(fewer, ATT_FULL_CHUNK)), pl.min_chunk);
+    const int longest = max((top + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, pl.min_chunk);
+    const int base = min((share + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT, longest);
+    const int more = (longest - base) / PLAN_UNIT;
+    auto cand = [&](int k) { return base + (more * (k * k) + 63 * 63 - 1) / (63 * 63) * PLAN_UNIT; };
+    const int ck = cand(lane);
+    int cnt = 0;
+    for (int b = wv; b < r.B; b += nt >> 6) cnt += max(1u, (unsigned)(s_it[b].ctx + ck - 1) / (unsigned)ck);
+    if (wv < r.B) atomicAdd(&s_cnt[lane], cnt);
     __syncthreads();
-    // a sequence's first item: the items of all sequences with longer chunks (ties: the lower index first)
-    const int parts = max(nt / r.B, 1);
-    for (int t = tid; t < r.B * parts; t += nt) {
-        const int b = t / parts, len = s_len[b];
-        int first = 0;
-#pragma unroll 8
-        for (int o = t - b * parts; o < r.B; o += parts) {
-            const int lo = s_len[o], no = s_nch[o];
-            first += lo > len || (lo == len && o < b) ? no : 0;
+    const uint64_t fits = __builtin_amdgcn_ballot_w64(s_cnt[lane] <= min(pl.target, pl.max_items));
+    const int ch = cand(fits ? (int)__builtin_ctzll(fits) : 63);
+    if (wv == 0) {                                             // items in the sequences' order
+        int items = 0;
+        for (int b0 = 0; b0 < r.B; b0 += 64) {
+            const int b = b0 + lane, ctx = b < r.B ? s_it[b].ctx : 0;
+            const int nch = b < r.B ? max(1u, (unsigned)(ctx + ch - 1) / (unsigned)ch) : 0;
+            int upto = nch;                                    // inclusive sum over the wave
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(upto, o, WAVE);
+                if (lane >= o) upto += v;
+            }
+            if (b < r.B) {
+                const int first = items + upto - nch;
+                s_first[b] = first;
+                s_nch[b] = nch;
+                s_len[b] = ((ctx + nch - 1) / nch + PLAN_UNIT - 1) / PLAN_UNIT * PLAN_UNIT;   // <= ch: no chunk is empty
+                pl.seq[b] = make_int2(first, nch);
+            }
+            items += __shfl(upto, 63, WAVE);
         }
-        atomicAdd(&s_first[b], first);
+        if (lane == 0) s_items = items;
     }
     __syncthreads();
-    for (int b = tid; b < r.B; b += nt) {
+    for (int b = wv; b < r.B; b += nt >> 6) {
         att_item it = s_it[b];
-        const int first = s_first[b], len = s_len[b], nch = s_nch[b];
-        it.nch = nch;
-        pl.seq[b] = make_int2(first, nch);
-        for (int c = 0; c < nch && first + c < pl.max_items; ++c) {
+        const int first = s_first[b], len = s_len[b];
+        it.nch = s_nch[b];
+        for (int c = lane; c < it.nch && first + c < pl.max_items; c += 64) {
             it.p0 = c * len;
             it.p1 = min(it.p0 + len, it.ctx);
             pl.item[first + c] = it;
@@ -1179,6 +1216,7 @@ att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32
     if (!kv_f32 && max_ctx <= ATT_FULL_CHUNK && p.max_items > B) p.max_items = B;
     p.whole = p.max_items == B;
     if (kv_f32) p.zs = 1;                                  // one work-group takes all of a KV head's query rows
+    p.in_order = p.whole && (B > PLAN_SEQS || (long long)B * n_kv * p.zs <= ATT_TARGET_WGS);
     return p;
 }
 

@@ -3,10 +3,11 @@ chunks by the sequences' own lengths, longest items first.
 
 A mirror of the rule picks the cases: a batch below the item target, in a
 cache much larger than its contexts, whose chunk starts fall 1 to 4 positions
-into the rows that a verify appends (so two work-groups write them), and a
-batch above the target (every sequence one item) with an empty sequence and an
-unusable slot among the others.  Logits against the oracle's forward over the
-same tokens, dense and paged."""
+into the rows that a verify appends (so two work-groups write them), a batch
+above the target (every sequence one item, longest first) with an empty sequence
+and an unusable slot among the others, and batches of one to four waves of
+sequences on two KV heads, cut or whole and in order.  Logits against the
+oracle's forward over the same tokens, dense and paged."""
 import numpy as np
 import pytest
 import torch
@@ -37,17 +38,17 @@ def chunks(ctx, n_kv):
     return [up(-(-x // -(-x // ch))) for x in ctx]
 
 
-def verify_against_oracle(lens, max_ctx, gamma, page, slots=None, check=None, seed=41, tol=2e-2):
+def verify_against_oracle(lens, max_ctx, gamma, page, slots=None, check=None, seed=41, tol=2e-2, cfg=CFG):
     B = len(lens)
-    W = synth.make_weights(CFG, seed, "cpu")
-    eng = sdrl.Engine(CFG, B, max_ctx, gamma)
+    W = synth.make_weights(cfg, seed, "cpu")
+    eng = sdrl.Engine(cfg, B, max_ctx, gamma)
     eng.bind_weights([w.cuda() for w in W])
     kv = DeviceKV(eng, max_ctx, page, seed)
     kv.fill_context(max(lens), seed + 100)
     kv.kv_len.copy_(i32(lens))
     torch.cuda.synchronize()
     kd0, vd0 = kv.dense()
-    V = CFG["vocab"]
+    V = cfg["vocab"]
     toks = synth.make_tokens(B, gamma + 1, V, seed + 1)
     p = torch.zeros((B, gamma + 1, V), dtype=torch.float32, device="cuda")
     eng.verify(i32(slots or range(B)), toks[:, 0].cuda().contiguous(), toks[:, 1:].cuda().contiguous(), gamma, p)
@@ -57,12 +58,12 @@ def verify_against_oracle(lens, max_ctx, gamma, page, slots=None, check=None, se
     else:
         eng.sync()
     kd, vd = kv.dense()
-    target, _ = oracle_models(CFG, host_bits(W))
+    target, _ = oracle_models(cfg, host_bits(W))
     pd = p.cpu().numpy()
     assert np.isfinite(pd).all()
     for b in check if check is not None else range(B):
         kl = lens[b]
-        okv = oracle_kv_from_device(CFG, kd0, vd0, b, kl, max_ctx)
+        okv = oracle_kv_from_device(cfg, kd0, vd0, b, kl, max_ctx)
         ol = oracle.forward_seq(target, okv, toks[b].numpy(), kl)
         for j in range(gamma + 1):
             assert np.abs(pd[b, j] - ol[j]).max() <= tol * np.abs(ol[j]).max(), (b, j)
@@ -109,3 +110,11 @@ def test_caches_on_either_side_of_the_short_rule(max_ctx):
     lens = [509, 0, 31, 257, 127, 128, 380]              # the longest fills the short cache
     say("short cache", max_ctx)
     verify_against_oracle(lens, max_ctx, 2, 0)
+
+
+@pytest.mark.parametrize("B", [63, 64, 65, 200, 255, 256])
+def test_batches_of_several_waves_of_sequences(B):
+    cfg = dict(CFG, name="plan-two-heads", n_q=2, n_kv=2)       # 256 items: 255 sequences are cut, 256 are not
+    lens = [(53 * b) % 97 + (900 if b % 50 == 7 else 0) for b in range(B)]
+    say("waves of sequences", B)
+    verify_against_oracle(lens, 1100, 2, 0, check=[0, 7, 57, 61, B - 2, B - 1], cfg=cfg)
