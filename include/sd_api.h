@@ -83,10 +83,8 @@ const char* sd_last_error(void);
 
 /* Creates an engine on the current HIP device.  max_slots: KV slots (and the
  * largest batch B); max_ctx: cached positions per slot; max_gamma: longest
- * draft.  The engine allocates its own workspace, sized for the larger of
- * max_slots*(max_gamma+1) and 2560 rows (a prefill's; where
- * memory has no room for those, the former). *out receives the
- * handle. */
+ * draft.  The engine allocates its own workspace, sized for
+ * max_slots*(max_gamma+1) rows. *out receives the handle. */
 sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32_t max_ctx, int32_t max_gamma,
                     sd_engine* out);
 sd_status sd_destroy(sd_engine e);
@@ -184,7 +182,11 @@ sd_status sd_refresh_drafter(sd_engine e, void* qbuf, size_t bytes, void* stream
 /* --------------------------------------------------------- the SD step */
 
 /* Target prefill: caches tokens[b*n + i] (device int32[B][n]) of sequence
- * slots[b] at positions kv_len + i, then kv_len += n. */
+ * slots[b] at positions kv_len + i, then kv_len += n.  The first prefill of more
+ * than max_slots*(max_gamma+1) rows allocates a workspace of 2560 rows, which
+ * the engine keeps, unless the stream is being captured, 2560 is not more, or it
+ * would take more than a quarter of the free device memory; prefills without it
+ * run in rounds of max_slots*(max_gamma+1) rows. */
 sd_status sd_prefill(sd_engine e, int32_t B, const int32_t* slots, const int32_t* tokens, int32_t n,
                      void* stream);
 

@@ -8,6 +8,7 @@
 
 #include <limits.h>
 
+#include <iterator>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -50,10 +51,24 @@ static sd_status launched(const char* what)
 enum { PRJ_QKV = 0, PRJ_O = 1, PRJ_GU = 2, PRJ_DOWN = 3 };
 enum { T_ATTN_D = 0, T_ATTN_V = 1, T_Q4 = 2, T_PROJ = 3, T_LMHEAD = 4, T_SAMPLE = 5, T_ACCEPT = 6, T_MISC = 7, T_CLASSES = 8 };
 
+// The buffers of one forward of up to `rows` rows.
+struct workspace {
+    int rows = 0;
+    float* h = nullptr;
+    void* a = nullptr;
+    float* qkv = nullptr;
+    float* qrot = nullptr;
+    void* att = nullptr;
+    float* gu = nullptr;
+    void* act = nullptr;
+    float* att_part = nullptr;
+    float* gpart = nullptr;      // split-K partial sums
+    size_t gpart_cap = 0;        // floats
+};
+
 struct sd_engine_s {
     sd_model_cfg c;
     int max_slots, max_ctx, max_gamma;
-    int rows_max;                // rows of one forward
     int dev;
     bool f32;
     int poison = 0;
@@ -71,23 +86,15 @@ struct sd_engine_s {
     std::vector<const uint8_t*> qz;    // [L*4] zero points (asymmetric format), else NULL
     int qfmt = QF_W4;                  // format of the last refresh
     bool drafter_ready = false;
-    // workspace (engine-owned)
-    float* h = nullptr;
-    void* a = nullptr;
-    float* qkv = nullptr;
-    float* qrot = nullptr;
-    void* att = nullptr;
-    float* gu = nullptr;
-    void* act = nullptr;
-    float* att_part = nullptr;
+    // engine-owned
+    workspace ws;                // of a step's rows
+    workspace pf;                // of a long prefill's rows, from the first one on
     void* plan = nullptr;        // the running forward's attention plan
     float* samp_part = nullptr;
     float* acc_work = nullptr;
     float2* rope = nullptr;
     uint32_t* err = nullptr;
     int32_t* pf_lim = nullptr;   // a ragged-prefill round's lim [max_slots], row0 [max_slots] and live [1]
-    float* gpart = nullptr;      // split-K partial sums
-    size_t gpart_cap = 0;        // floats
     int launch_err = 0;          // a GEMM shape the kernels refused (reported by sd_sync)
     // kernel timing (diagnostics)
     bool timing = false;
@@ -205,32 +212,89 @@ extern "C" size_t sd_drafter_bytes_fmt(const sd_model_cfg* c, int32_t fmt)
 
 extern "C" size_t sd_drafter_bytes(const sd_model_cfg* c) { return sd_drafter_bytes_fmt(c, SD_DRAFT_W4); }
 
-// Largest split-K scratch any projection or the LM head needs for up to R rows:
-// of every row count of a step, and of every 16th of a longer prefill's (where
-// the scratch falls short, that projection runs unsplit).
-static size_t gpart_bytes(const sd_model_cfg& c, int step_rows, int R)
+// Largest split-K scratch (bytes) of a step's forwards: the target's projections
+// and the LM head up to `rows` rows, the drafter's projections up to `drafts`.
+static size_t gpart_bytes(const sd_model_cfg& c, int rows, int drafts)
 {
     if (c.dtype == SD_DTYPE_F32) return 256;
-    size_t mx = 0;
-    for (int m = 1; m <= R; m += m < step_rows ? 1 : 16) {
-        size_t f = gemm_part_floats(m, c.vocab, c.hidden);
-        mx = f > mx ? f : mx;
+    size_t mx = 64;
+    auto take = [&](size_t f) { mx = f > mx ? f : mx; };
+    for (int m = 1; m <= rows; ++m) {
+        take(gemm_part_floats(m, c.vocab, c.hidden));
         for (int w = 0; w < 4; ++w) {
             int N, K;
             prj_shape(c, w, &N, &K);
-            f = gemm_part_floats(m, N, K);
-            mx = f > mx ? f : mx;
-            f = gemm_q4_part_floats(m, N, K);
-            mx = f > mx ? f : mx;
+            take(gemm_part_floats(m, N, K));
+            if (m <= drafts) take(gemm_q4_part_floats(m, N, K));
         }
     }
-    return (mx > 64 ? mx : 64) * 4;
+    return mx * 4;
+}
+
+// The same of a prefill's: the projections at every 16th row count (where the
+// scratch falls short, a projection runs unsplit).
+static size_t prefill_gpart_bytes(const sd_model_cfg& c, int rows)
+{
+    if (c.dtype == SD_DTYPE_F32) return 256;
+    size_t mx = 64;
+    for (int m = 16; m <= rows; m += 16)
+        for (int w = 0; w < 4; ++w) {
+            int N, K;
+            prj_shape(c, w, &N, &K);
+            const size_t f = gemm_part_floats(m, N, K);
+            mx = f > mx ? f : mx;
+        }
+    return mx * 4;
+}
+
+struct ws_block { void** p; size_t bytes; };
+
+// A prefill's buffers hold the target's activations only (bf16 ones in two
+// bytes), and no gate/up: its SwiGLU is fused or reads the split partials.
+static std::vector<ws_block> ws_blocks(const sd_model_cfg& c, int max_slots, bool prefill, workspace& w)
+{
+    const size_t R = (size_t)w.rows, qkvN = (size_t)(c.n_q + 2 * c.n_kv) * c.head_dim, qd = (size_t)c.n_q * c.head_dim;
+    const bool f32 = c.dtype == SD_DTYPE_F32;
+    const size_t el = prefill && !f32 ? 2 : 4;
+    const size_t gp = prefill ? prefill_gpart_bytes(c, w.rows) : gpart_bytes(c, w.rows, max_slots);
+    w.gpart_cap = gp / 4;
+    std::vector<ws_block> b = {
+        {(void**)&w.h, R * c.hidden * 4},
+        {(void**)&w.a, R * c.hidden * el},
+        {(void**)&w.qkv, R * qkvN * 4},
+        {(void**)&w.qrot, R * qd * 4},
+        {(void**)&w.att, R * qd * el},
+        {(void**)&w.act, R * c.ffn * el},
+        {(void**)&w.att_part, attention_part_floats(w.rows, c.n_q, c.n_kv, c.head_dim, f32) * 4},
+        {(void**)&w.gpart, gp},
+    };
+    if (!prefill || f32) b.push_back({(void**)&w.gu, R * 2 * (size_t)c.ffn * 4});
+    return b;
+}
+
+// All of the blocks or none; the failed one's bytes, or 0.
+static size_t alloc_blocks(const std::vector<ws_block>& b)
+{
+    for (size_t i = 0; i < b.size(); ++i) {
+        if (hipMalloc(b[i].p, b[i].bytes) == hipSuccess) continue;
+        (void)hipGetLastError();
+        for (size_t k = 0; k <= i; ++k) {
+            if (k < i) (void)hipFree(*b[k].p);
+            *b[k].p = nullptr;
+        }
+        return b[i].bytes;
+    }
+    return 0;
 }
 
 static void free_ws(sd_engine e)
 {
-    void* ps[] = {e->h, e->a, e->qkv, e->qrot, e->att, e->gu, e->act, e->att_part, e->plan, e->samp_part, e->acc_work, e->rope, e->err,
-                  e->pf_lim, e->gpart};
+    for (workspace* w : {&e->ws, &e->pf}) {
+        void* ps[] = {w->h, w->a, w->qkv, w->qrot, w->att, w->gu, w->act, w->att_part, w->gpart};
+        for (void* p : ps)
+            if (p) (void)hipFree(p);
+    }
+    void* ps[] = {e->plan, e->samp_part, e->acc_work, e->rope, e->err, e->pf_lim};
     for (void* p : ps)
         if (p) (void)hipFree(p);
 }
@@ -239,9 +303,39 @@ static void free_ws(sd_engine e)
 // a pass over the weights (8B gate/up: 98 us and 690 TFLOP/s at the 288 rows of
 // 24 sequences drafting up to 11, 292 us and 1030 TFLOP/s at 1280; 24 prompts of
 // 170-511 tokens in 36.0, 20.1, 17.3 and 18.5 ms with 288, 1280, 2560 and 3840
-// rows).  The workspace this takes, .7 MB a row at the 32B shape, is 0.6% of
-// the memory; where it does not fit, prefills run in the step's rows.
+// rows).
 constexpr int PREFILL_ROWS = 2560;
+
+// The workspace for a prefill of `rows` rows in all.  One of PREFILL_ROWS (599 MB
+// at the 32B shape, 384 at the 8B shape) is taken by the first prefill that does
+// not fit a step's rows, since the KV cache is there by then and an engine that
+// never prefills needs none; only where it is at most a quarter of the free
+// memory, and not while the stream is being captured.  The thread's capture mode
+// is relaxed meanwhile: another thread's capture does not use these buffers.
+static workspace& prefill_ws(sd_engine e, long long rows, hipStream_t s)
+{
+    if (rows <= e->ws.rows || PREFILL_ROWS <= e->ws.rows || e->no_fuse) return e->ws;
+    if (e->pf.rows) return e->pf;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return e->ws;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return e->ws;
+    }
+    workspace w;
+    w.rows = PREFILL_ROWS;
+    const std::vector<ws_block> blocks = ws_blocks(e->c, e->max_slots, true, w);
+    size_t need = 0, avail = 0, total = 0;
+    for (const ws_block& b : blocks) need += b.bytes;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) (void)hipGetLastError();
+    else if (need <= avail / 4 && !alloc_blocks(blocks)) e->pf = w;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e->pf.rows ? e->pf : e->ws;
+}
 
 extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32_t max_ctx, int32_t max_gamma,
                                sd_engine* out)
@@ -256,8 +350,7 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     e->max_slots = max_slots;
     e->max_ctx = max_ctx;
     e->max_gamma = max_gamma;
-    const int step_rows = max_slots * (max_gamma + 1);
-    e->rows_max = step_rows > PREFILL_ROWS ? step_rows : PREFILL_ROWS;
+    e->ws.rows = max_slots * (max_gamma + 1);
     e->f32 = cfg->dtype == SD_DTYPE_F32;
     e->w.assign(sd_num_weights(cfg), nullptr);
     e->qw.assign(4 * cfg->n_layers, nullptr);
@@ -266,42 +359,19 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     if (hipGetDevice(&e->dev) != hipSuccess) { delete e; return fail(SD_E_HIP, "hipGetDevice failed"); }
 
     const sd_model_cfg& c = *cfg;
-    int qkvN = (c.n_q + 2 * c.n_kv) * c.head_dim, qd = c.n_q * c.head_dim;
-    for (bool fits = false; !fits;) {
-        const size_t R = (size_t)e->rows_max;
-        e->gpart_cap = gpart_bytes(c, step_rows, e->rows_max) / 4;
-        struct { void** p; size_t bytes; } allocs[] = {
-            {(void**)&e->h, R * c.hidden * 4},
-            {(void**)&e->a, R * c.hidden * 4},
-            {(void**)&e->qkv, R * qkvN * 4},
-            {(void**)&e->qrot, R * qd * 4},
-            {(void**)&e->att, R * qd * 4},
-            {(void**)&e->gu, R * 2 * (size_t)c.ffn * 4},
-            {(void**)&e->act, R * c.ffn * 4},
-            {(void**)&e->att_part, attention_part_floats((int)R, c.n_q, c.n_kv, c.head_dim, e->f32) * 4},
-            {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
-            {(void**)&e->samp_part, sample_part_floats(step_rows, c.vocab) * 4},
-            {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
-            {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
-            {(void**)&e->err, ERR_COUNT * 4},
-            {(void**)&e->pf_lim, ((size_t)2 * max_slots + 1) * 4},
-            {(void**)&e->gpart, e->gpart_cap * 4},
-        };
-        fits = true;
-        for (auto& al : allocs) {
-            if (hipMalloc(al.p, al.bytes) == hipSuccess) continue;
-            (void)hipGetLastError();
-            *al.p = nullptr;
-            free_ws(e);
-            for (auto& done : allocs) *done.p = nullptr;
-            if (e->rows_max == step_rows) {
-                delete e;
-                return fail(SD_E_NOMEM, "workspace allocation of %zu bytes failed", al.bytes);
-            }
-            e->rows_max = step_rows;
-            fits = false;
-            break;
-        }
+    std::vector<ws_block> blocks = ws_blocks(c, max_slots, false, e->ws);
+    const ws_block more[] = {
+        {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
+        {(void**)&e->samp_part, sample_part_floats(e->ws.rows, c.vocab) * 4},
+        {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
+        {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
+        {(void**)&e->err, ERR_COUNT * 4},
+        {(void**)&e->pf_lim, ((size_t)2 * max_slots + 1) * 4},
+    };
+    blocks.insert(blocks.end(), std::begin(more), std::end(more));
+    if (const size_t failed = alloc_blocks(blocks)) {
+        delete e;
+        return fail(SD_E_NOMEM, "workspace allocation of %zu bytes failed", failed);
     }
     // RoPE table: cos/sin(pos * theta^(-2i/d)) computed in double on the host
     int hd = c.head_dim / 2;
@@ -439,10 +509,10 @@ extern "C" sd_status sd_refresh_drafter(sd_engine e, void* qbuf, size_t bytes, v
 // ------------------------------------------------------------------ forward
 static act_t act_of(sd_engine e, bool draft) { return e->f32 ? ACT_F32 : (draft ? ACT_F16 : ACT_BF16); }
 
-// Returns the K splits of a deferred split-K projection (partials in gpart),
+// Returns the K splits of a deferred split-K projection (partials in ws.gpart),
 // or 1 when C holds the result.
-static int proj(sd_engine e, bool draft, int layer, int which, const void* A, float* C, int M, int ldc, gemm_mode mode,
-                hipStream_t s, const int32_t* live)
+static int proj(sd_engine e, const workspace& ws, bool draft, int layer, int which, const void* A, float* C, int M, int ldc,
+                gemm_mode mode, hipStream_t s, const int32_t* live)
 {
     int N, K;
     prj_shape(e->c, which, &N, &K);
@@ -452,21 +522,21 @@ static int proj(sd_engine e, bool draft, int layer, int which, const void* A, fl
         const uint16_t* sc = e->qs[4 * layer + which];
         const uint8_t* z = e->qz[4 * layer + which];
         if (e->f32) { launch_gemm_q4_f32((const float*)A, q, sc, z, e->qfmt, C, M, N, K, ldc, mode, s); return 1; }
-        const int S = launch_gemm_q4((const uint16_t*)A, q, sc, z, e->qfmt, C, e->gpart, e->gpart_cap, M, N, K, ldc,
+        const int S = launch_gemm_q4((const uint16_t*)A, q, sc, z, e->qfmt, C, ws.gpart, ws.gpart_cap, M, N, K, ldc,
                                      mode, s);
         if (S < 1) e->launch_err = 1;   // cannot happen for a configuration check_cfg accepted
         return S < 1 ? 1 : S;
     }
     const void* w = W(e, layer, widx[which]);
     if (e->f32) { launch_gemm_f32((const float*)A, (const float*)w, C, M, N, K, ldc, mode, s); return 1; }
-    return launch_gemm_bf16((const uint16_t*)A, (const uint16_t*)w, C, e->gpart, e->gpart_cap, M, N, K, ldc, mode, true, s,
+    return launch_gemm_bf16((const uint16_t*)A, (const uint16_t*)w, C, ws.gpart, ws.gpart_cap, M, N, K, ldc, mode, true, s,
                             !e->no_dma, live);
 }
 
 // The gate/up projection with SwiGLU in its epilogue, writing act directly;
 // false when the shape has no fused kernel (or fusion is switched off).
-static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void* act, act_t at, int M, hipStream_t s,
-                        const int32_t* live)
+static bool proj_swiglu(sd_engine e, const workspace& ws, bool draft, int layer, const void* A, void* act, act_t at, int M,
+                        hipStream_t s, const int32_t* live)
 {
     if (e->f32 || e->no_fuse) return false;
     const sd_model_cfg& c = e->c;
@@ -476,7 +546,7 @@ static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void*
                                      c.hidden, s) != 0;
     }
     return launch_gemm_bf16_swiglu((const uint16_t*)A, (const uint16_t*)W(e, layer, 4), act, at, M, c.ffn, c.hidden,
-                                   s, !e->no_dma, live) != 0;
+                                   ws.gpart_cap, s, !e->no_dma, live) != 0;
 }
 
 // One forward pass over B sequences x n tokens (row r = b*n + i at position
@@ -485,7 +555,7 @@ static bool proj_swiglu(sd_engine e, bool draft, int layer, const void* A, void*
 // otherwise the last layer's FFN (which only feeds the logits) is skipped.
 // packed: the rows of a ragged-prefill round (rows_t), set up by
 // launch_prefill_lim.
-static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const int32_t* tokA, int sA,
+static void forward(sd_engine e, const workspace& ws, bool draft, int B, const int32_t* slots, const int32_t* tokA, int sA,
                     const int32_t* tokB, int sB, int n, int off, float* logits, long ldl, hipStream_t s,
                     bool packed = false)
 {
@@ -505,41 +575,41 @@ static void forward(sd_engine e, bool draft, int B, const int32_t* slots, const 
     attention_plan_bind(plan, e->plan, e->max_slots);
     int S;
     { tscope t(e, T_MISC, s);
-      launch_embed_rmsnorm(r, tokA, sA, tokB, sB, e->w[0], e->f32, c.hidden, c.vocab, e->h, W(e, 0, 0), c.rms_eps, e->a, at, plan, s); }
+      launch_embed_rmsnorm(r, tokA, sA, tokB, sB, e->w[0], e->f32, c.hidden, c.vocab, ws.h, W(e, 0, 0), c.rms_eps, ws.a, at, plan, s); }
     for (int l = 0; l < c.n_layers; ++l) {
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_QKV, e->a, e->qkv, R, qkvN, GEMM_STORE, s, r.live); }
+        { tscope t(e, pcls, s); S = proj(e, ws, draft, l, PRJ_QKV, ws.a, ws.qkv, R, qkvN, GEMM_STORE, s, r.live); }
         if (!logits && l == c.n_layers - 1) {
             // the rest of the last layer only feeds the logits: the new K/V rows alone
             tscope t(e, T_MISC, s);
-            launch_rope_kv(r, e->qkv, e->gpart, S, e->rope, c.n_q, kv, l, e->qrot, s);
+            launch_rope_kv(r, ws.qkv, ws.gpart, S, e->rope, c.n_q, kv, l, ws.qrot, s);
             break;
         }
         { kscope t(e, n == 1 ? T_ATTN_D : T_ATTN_V);      // RoPE and the new K/V rows are part of the attention
-          launch_attention(r, plan, qkv_src{e->qkv, e->gpart, S, e->rope}, e->qrot, c.n_q, kv, l, e->att_part, e->att, at,
+          launch_attention(r, plan, qkv_src{ws.qkv, ws.gpart, S, e->rope}, ws.qrot, c.n_q, kv, l, ws.att_part, ws.att, at,
                            s, t.start, t.stop); }
         if (!plan.whole) {
             tscope t(e, T_MISC, s);
-            launch_attention_combine(r, plan, c.n_q, c.n_kv, c.head_dim, e->att_part, e->att, at, s);
+            launch_attention_combine(r, plan, c.n_q, c.n_kv, c.head_dim, ws.att_part, ws.att, at, s);
         }
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_O, e->att, e->h, R, c.hidden, GEMM_ADD, s, r.live); }
-        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, W(e, l, 3), e->f32, c.rms_eps, e->a, at, r.live, s); }
+        { tscope t(e, pcls, s); S = proj(e, ws, draft, l, PRJ_O, ws.att, ws.h, R, c.hidden, GEMM_ADD, s, r.live); }
+        { tscope t(e, T_MISC, s); launch_add_rmsnorm(ws.h, ws.gpart, S, R, c.hidden, W(e, l, 3), e->f32, c.rms_eps, ws.a, at, r.live, s); }
         bool fused;
-        { tscope t(e, pcls, s); fused = proj_swiglu(e, draft, l, e->a, e->act, at, R, s, r.live); }
+        { tscope t(e, pcls, s); fused = proj_swiglu(e, ws, draft, l, ws.a, ws.act, at, R, s, r.live); }
         if (!fused) {
-            { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_GU, e->a, e->gu, R, 2 * c.ffn, GEMM_STORE, s, r.live); }
-            { tscope t(e, T_MISC, s); launch_silu_mul(e->gu, e->gpart, S, R, c.ffn, e->act, at, r.live, s); }
+            { tscope t(e, pcls, s); S = proj(e, ws, draft, l, PRJ_GU, ws.a, ws.gu, R, 2 * c.ffn, GEMM_STORE, s, r.live); }
+            { tscope t(e, T_MISC, s); launch_silu_mul(ws.gu, ws.gpart, S, R, c.ffn, ws.act, at, r.live, s); }
         }
-        { tscope t(e, pcls, s); S = proj(e, draft, l, PRJ_DOWN, e->act, e->h, R, c.hidden, GEMM_ADD, s, r.live); }
+        { tscope t(e, pcls, s); S = proj(e, ws, draft, l, PRJ_DOWN, ws.act, ws.h, R, c.hidden, GEMM_ADD, s, r.live); }
         // next layer's attention norm, or the final norm (the LM head stays in the target precision)
         const bool last = l == c.n_layers - 1;
         const act_t nt = last ? (e->f32 ? ACT_F32 : ACT_BF16) : at;
         const void* g = last ? e->w[1] : W(e, l + 1, 0);
-        { tscope t(e, T_MISC, s); launch_add_rmsnorm(e->h, e->gpart, S, R, c.hidden, g, e->f32, c.rms_eps, e->a, nt, r.live, s); }
+        { tscope t(e, T_MISC, s); launch_add_rmsnorm(ws.h, ws.gpart, S, R, c.hidden, g, e->f32, c.rms_eps, ws.a, nt, r.live, s); }
     }
     if (logits) {
         tscope t(e, T_LMHEAD, s);
-        if (e->f32) launch_gemm_f32((const float*)e->a, (const float*)e->w[2], logits, R, c.vocab, c.hidden, (int)ldl, GEMM_STORE, s);
-        else launch_gemm_bf16((const uint16_t*)e->a, (const uint16_t*)e->w[2], logits, e->gpart, e->gpart_cap, R, c.vocab,
+        if (e->f32) launch_gemm_f32((const float*)ws.a, (const float*)e->w[2], logits, R, c.vocab, c.hidden, (int)ldl, GEMM_STORE, s);
+        else launch_gemm_bf16((const uint16_t*)ws.a, (const uint16_t*)e->w[2], logits, ws.gpart, ws.gpart_cap, R, c.vocab,
                                 c.hidden, (int)ldl, GEMM_STORE, false, s, !e->no_dma);
     }
 }
@@ -563,10 +633,11 @@ extern "C" sd_status sd_prefill(sd_engine e, int32_t B, const int32_t* slots, co
     if (!tokens || n < 1) return fail(SD_E_INVAL, "need tokens and n >= 1");
     if (n > e->max_ctx) return fail(SD_E_INVAL, "n=%d exceeds max_ctx=%d", n, e->max_ctx);
     hipStream_t s = (hipStream_t)stream;
-    int chunk = e->rows_max / B;
+    const workspace& ws = prefill_ws(e, (long long)B * n, s);
+    int chunk = ws.rows / B;
     for (int t0 = 0; t0 < n; t0 += chunk) {
         int nc = n - t0 < chunk ? n - t0 : chunk;
-        forward(e, false, B, slots, tokens + t0, n, tokens + t0 + 1, n, nc, 0, nullptr, 0, s);
+        forward(e, ws, false, B, slots, tokens + t0, n, tokens + t0 + 1, n, nc, 0, nullptr, 0, s);
         launch_kv_advance(B, slots, nullptr, nc, e->kv_len, e->max_slots, e->err, s);
     }
     return launched("sd_prefill");
@@ -582,12 +653,13 @@ extern "C" sd_status sd_prefill_ragged(sd_engine e, int32_t B, const int32_t* sl
     hipStream_t s = (hipStream_t)stream;
     // rounds of up to nc positions of every sequence, the rows of those that
     // still have tokens packed
-    int chunk = e->rows_max / B;
+    const workspace& ws = prefill_ws(e, (long long)B * ld, s);
+    int chunk = ws.rows / B;
     for (int t0 = 0; t0 < ld; t0 += chunk) {
         int nc = ld - t0 < chunk ? ld - t0 : chunk;
         launch_prefill_lim(B, len, t0, nc, ld, e->pf_lim, e->pf_lim + e->max_slots, e->pf_lim + 2 * e->max_slots,
                            e->err, s);
-        forward(e, false, B, slots, tokens + t0, ld, tokens + t0 + 1, ld, nc, 0, nullptr, 0, s, true);
+        forward(e, ws, false, B, slots, tokens + t0, ld, tokens + t0 + 1, ld, nc, 0, nullptr, 0, s, true);
         launch_kv_advance(B, slots, e->pf_lim, 0, e->kv_len, e->max_slots, e->err, s);
     }
     return launched("sd_prefill_ragged");
@@ -616,7 +688,7 @@ extern "C" sd_status sd_draft(sd_engine e, int32_t B, const int32_t* slots, cons
         const int32_t* tok = j == 1 ? last_tok : draft_tok + (j - 2);
         int stride = j == 1 ? 1 : gamma;
         float* lg = q_logits + (size_t)(j - 1) * V;
-        forward(e, true, B, slots, tok, stride, tok, stride, 1, j - 1, lg, ld, s);
+        forward(e, e->ws, true, B, slots, tok, stride, tok, stride, 1, j - 1, lg, ld, s);
         tscope t(e, T_SAMPLE, s);
         launch_sample(r, lg, ld, V, T, rg, j, draft_tok + (j - 1), gamma, q_stats + 2 * (j - 1), 2 * gamma,
                       e->samp_part, s);
@@ -631,7 +703,7 @@ extern "C" sd_status sd_verify(sd_engine e, int32_t B, const int32_t* slots, con
     if (st != SD_OK) return st;
     if ((st = check_gamma(e, gamma, 1.0f)) != SD_OK) return st;
     if (!last_tok || !draft_tok || !p_logits) return fail(SD_E_INVAL, "NULL buffer");
-    forward(e, false, B, slots, last_tok, 1, draft_tok, gamma, gamma + 1, 0, p_logits, e->c.vocab,
+    forward(e, e->ws, false, B, slots, last_tok, 1, draft_tok, gamma, gamma + 1, 0, p_logits, e->c.vocab,
             (hipStream_t)stream);
     return launched("sd_verify");
 }
@@ -738,7 +810,7 @@ extern "C" sd_status sd_ar_step(sd_engine e, int32_t B, const int32_t* slots, co
     if (!(T > 0.f) || !isfinite(T)) return fail(SD_E_INVAL, "temperature must be finite and > 0");
     if (!last_tok || !out_tok || !p_logits) return fail(SD_E_INVAL, "NULL buffer");
     hipStream_t s = (hipStream_t)stream;
-    forward(e, false, B, slots, last_tok, 1, last_tok, 1, 1, 0, p_logits, e->c.vocab, s);
+    forward(e, e->ws, false, B, slots, last_tok, 1, last_tok, 1, 1, 0, p_logits, e->c.vocab, s);
     rows_t r = {B, 1, 0, slots, e->kv_len, e->max_slots, e->max_ctx, e->err};
     rng_t rg = {rng.seed, rng.step};
     { tscope t(e, T_SAMPLE, s); launch_sample(r, p_logits, e->c.vocab, e->c.vocab, T, rg, 1, out_tok, 1, nullptr, 0, e->samp_part, s); }

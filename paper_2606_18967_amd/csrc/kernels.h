@@ -133,10 +133,11 @@ int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part
 // The gate/up projection with SwiGLU in its epilogue: out[M][F] (type out_t)
 // = SiLU(g) * u, [g | u] = A W^T with W [2F][K] (gate rows, then up rows).
 // Returns 1 when launched, 0 when the shape has no fused kernel (the caller
-// then runs the plain GEMM and launch_silu_mul).  The int4 form takes the
+// then runs the plain GEMM and launch_silu_mul).  part_cap: the scratch that
+// the plain GEMM would have, by which it splits or not.  The int4 form takes the
 // packed drafter layout of kernels_q4.hip.
 int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act_t out_t, int M, int F, int K,
-                            hipStream_t s, bool lds_dma = true, const int32_t* live = nullptr);
+                            size_t part_cap, hipStream_t s, bool lds_dma = true, const int32_t* live = nullptr);
 int launch_gemm_q4_swiglu(const uint16_t* A, const uint32_t* Wq, const uint16_t* Sc, const uint8_t* Z, int fmt,
                           void* out, act_t out_t, int M, int F, int K, hipStream_t s);
 size_t gemm_part_floats(int M, int N, int K);

@@ -894,14 +894,15 @@ int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part
 }
 
 int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act_t out_t, int M, int F, int K,
-                            hipStream_t s, bool lds_dma, const int32_t* live)
+                            size_t part_cap, hipStream_t s, bool lds_dma, const int32_t* live)
 {
     const int N = 2 * F;
     if (!use_dma(N, K) || F % 64) return 0;
     // fused only where the plain projection runs unsplit (the same products
     // summed in the same order either way)
-    const dma_tile p = dma_plan(M, N, K);
-    if (p.S != 1 || F % (32 * p.wcn)) return 0;
+    dma_tile p = dma_plan(M, N, K);
+    if ((p.S > 1 && (size_t)p.S * M * N <= part_cap) || F % (32 * p.wcn)) return 0;
+    p.S = 1;
     if (lds_dma || p.mt != 10) {
         dma_launch<true>({A, W, nullptr, nullptr, M, N, K, 0, 0, out, (int)out_t, live}, p, s);
     } else {
