@@ -62,7 +62,7 @@ struct att_plan {
     int max_items;         // grid size: max(target, B), fewer where max_ctx allows no more
     bool whole;            // every sequence is one item: no combine
     bool in_order;         // and the items are in the sequences' order
-    int mq, zs;            // query tiles per work-group and query-row slices (bf16 cache)
+    int mq, zs;            // 16-row query tiles per work-group, query-row slices
 };
 // the launch geometry of B sequences x n rows (no device pointers)
 att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32);
