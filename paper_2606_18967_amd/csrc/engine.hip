@@ -57,7 +57,7 @@ struct workspace {
     float* h = nullptr;
     void* a = nullptr;
     float* qkv = nullptr;
-    float* qrot = nullptr;
+    float* qrot = nullptr;       // rotated queries (fp32 cache)
     void* att = nullptr;
     float* gu = nullptr;
     void* act = nullptr;
@@ -262,12 +262,12 @@ static std::vector<ws_block> ws_blocks(const sd_model_cfg& c, int max_slots, boo
         {(void**)&w.h, R * c.hidden * 4},
         {(void**)&w.a, R * c.hidden * el},
         {(void**)&w.qkv, R * qkvN * 4},
-        {(void**)&w.qrot, R * qd * 4},
         {(void**)&w.att, R * qd * el},
         {(void**)&w.act, R * c.ffn * el},
         {(void**)&w.att_part, attention_part_floats(w.rows, c.n_q, c.n_kv, c.head_dim, f32) * 4},
         {(void**)&w.gpart, gp},
     };
+    if (f32) b.push_back({(void**)&w.qrot, R * qd * 4});
     if (!prefill || f32) b.push_back({(void**)&w.gu, R * 2 * (size_t)c.ffn * 4});
     return b;
 }
@@ -303,11 +303,11 @@ static void free_ws(sd_engine e)
 // a pass over the weights (8B gate/up: 98 us and 690 TFLOP/s at the 288 rows of
 // 24 sequences drafting up to 11, 292 us and 1030 TFLOP/s at 1280; 24 prompts of
 // 170-511 tokens in 36.0, 20.1, 17.3 and 18.5 ms with 288, 1280, 2560 and 3840
-// rows).
+// rows; one prompt of 2500 in 4.5 ms, in steps' 320 rows 14.1).
 constexpr int PREFILL_ROWS = 2560;
 
-// The workspace for a prefill of `rows` rows in all.  One of PREFILL_ROWS (599 MB
-// at the 32B shape, 384 at the 8B shape) is taken by the first prefill that does
+// The workspace for a prefill of `rows` rows in all.  One of PREFILL_ROWS (546 MB
+// at the 32B shape, 342 at the 8B shape) is taken by the first prefill that does
 // not fit a step's rows, since the KV cache is there by then and an engine that
 // never prefills needs none; only where it is at most a quarter of the free
 // memory, and not while the stream is being captured.  The thread's capture mode
@@ -581,7 +581,7 @@ static void forward(sd_engine e, const workspace& ws, bool draft, int B, const i
         if (!logits && l == c.n_layers - 1) {
             // the rest of the last layer only feeds the logits: the new K/V rows alone
             tscope t(e, T_MISC, s);
-            launch_rope_kv(r, ws.qkv, ws.gpart, S, e->rope, c.n_q, kv, l, ws.qrot, s);
+            launch_rope_kv(r, ws.qkv, ws.gpart, S, e->rope, c.n_q, kv, l, nullptr, s);
             break;
         }
         { kscope t(e, n == 1 ? T_ATTN_D : T_ATTN_V);      // RoPE and the new K/V rows are part of the attention

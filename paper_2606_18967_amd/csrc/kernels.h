@@ -62,6 +62,7 @@ struct att_plan {
     int max_items;         // grid size: max(target, B), fewer where max_ctx allows no more
     bool whole;            // every sequence is one item: no combine
     bool in_order;         // and the items are in the sequences' order
+    bool kv_first;         // the new K/V rows are stored by a launch before the attention (bf16 cache)
     int mq, zs;            // 16-row query tiles per work-group, query-row slices
 };
 // the launch geometry of B sequences x n rows (no device pointers)
@@ -79,6 +80,7 @@ void launch_embed_rmsnorm(const rows_t& r, const int32_t* tokA, int sA, const in
 // (live as rows_t::live)
 void launch_add_rmsnorm(float* h, const float* P, int S, int R, int H, const void* gain, int g_f32,
                         float eps, void* out, act_t out_t, const int32_t* live, hipStream_t s);
+// q_out NULL: the K/V rows alone
 void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, const float2* rope, int n_q,
                     const cache_t& c, int layer, float* q_out, hipStream_t s);
 // Attention in two launches: each item's softmax-weighted sums (the output
@@ -88,13 +90,15 @@ void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, co
 // partials P) with the RoPE table.  The attention applies RoPE and writes the
 // new rows: with a bf16 cache the attention kernel itself rotates its query
 // rows and writes its KV head's new K (rotated) and V rows of its context
-// range before reading them; with an fp32 cache k_rope_kv runs first, writing
-// the rotated queries into q (scratch, [rows][n_q][head_dim] fp32).
+// range before reading them, unless k_rope_kv has stored them (att_plan::kv_first);
+// with an fp32 cache k_rope_kv runs first, writing the rotated queries into q
+// (scratch, [rows][n_q][head_dim] fp32).
 struct qkv_src {
     const float* qkv;
     const float* P;
     int S;
     const float2* rope;
+    bool stored = false;     // the new K/V rows are in the cache (att_plan::kv_first)
 };
 // ev0/ev1, when given, are bound to the attention kernel's own dispatch
 // (hipExtLaunchKernelGGL): their elapsed time is the kernel's run time.

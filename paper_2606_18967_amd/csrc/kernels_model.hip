@@ -326,19 +326,19 @@ __device__ __forceinline__ long long hbase_of(const kv_geom& g, int layer, int k
 // units of d columns.  RoPE rotate-half with the (cos, sin) table
 // rope[pos][d/2].  q_out gets the rotated queries (fp32); the rotated keys and
 // the values go to the cache at the row's position.  Work-group (row, group
-// of upw head units); each thread takes one (unit, k) pair, columns k and
-// k + d/2 of the unit.
+// of upw head units, from unit first on: 0, or n_q for K and V alone); each
+// thread takes one (unit, k) pair, columns k and k + d/2 of the unit.
 template <typename T>
 __global__ void __launch_bounds__(256) k_rope_kv(rows_t r, const float* qkv, const float* P, int S, const float2* rope,
                                                  int n_q, int n_kv, int d, T* kc, T* vc, kv_geom g, int layer,
-                                                 float* q_out, int upw)
+                                                 float* q_out, int first, int upw)
 {
     int b, i, slot, pos;
     const bool ok = row_geom(r, blockIdx.x, &b, &i, &slot, &pos);
     if (r.lim && i >= r.lim[b]) return;
     const int row = r.row0 ? r.row0[b] + i : (int)blockIdx.x;
     const int hd = d / 2, units = n_q + 2 * n_kv;
-    const int u0 = blockIdx.y * upw, nu = min(upw, units - u0);
+    const int u0 = first + blockIdx.y * upw, nu = min(upw, units - u0);
     const size_t RN = (size_t)r.B * r.n * units * d;
     const size_t base_idx = (size_t)row * units * d;
     float* qo = q_out + (size_t)row * n_q * d;
@@ -542,11 +542,23 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 #ifndef ATT_INTERLEAVE
 #define ATT_INTERLEAVE 1
 #endif
-// K and V are read once per launch: non-temporal loads (cache policy bit 1,
-// nt on this target) stream them past the caches, which HBM serves faster
-// (7.2 against 6.4 TB/s for plain 16-byte streaming loads measured on this part)
+// K and V are read once per launch where a KV head's query rows are one slice:
+// non-temporal loads (cache policy bit 1, nt on this target) stream them past
+// the caches, which HBM serves faster (7.2 against 6.4 TB/s for plain 16-byte
+// streaming loads measured on this part).  Several slices read them again;
+// plain loads there are worth 0 to 2% of a prefill, which is not another build
+// of the kernel.
 #ifndef ATT_NT
 #define ATT_NT 2
+#endif
+// From how many query-row slices on the new K/V rows are stored by a launch of
+// their own.  Below, each slice stores what it reads, which costs less than the
+// launch or as much: prefill of 64 x 40 rows (three slices, four layers of the 8B
+// shape) 4010 us either way.  Past it the repeated rows cost more: 24 x 106 rows
+// (seven) 4028 against 4135, one prompt of 2500 (157) 4491 against 6438, and 8984
+// where each slice also walked the positions past its rows.
+#ifndef ATT_KV_SLICES
+#define ATT_KV_SLICES 2
 #endif
 #ifndef ATT_TARGET_WGS
 #define ATT_TARGET_WGS 512
@@ -563,9 +575,11 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 // QKV projection's output (qkv_src, kernels.h) each work-group forms its
 // rotated query rows and writes its KV head's new K (rotated) and V rows of
 // its context range to the cache before its waves read them (each
-// work-group of the head covering new positions writes those it reads;
-// query-row slices of one chunk write the same values), and it raises the
-// slot, position and page flags for them.
+// work-group of the head covering new positions writes those it reads; two
+// query-row slices of one chunk write the same values, and with more of them
+// k_rope_kv has stored the rows before, qs.stored), and it raises the slot,
+// position and page flags for them.  A slice's walk ends at the last position
+// that its rows attend.
 template <int D, int MQ, bool PAGED>
 __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, int n_q, int n_kv, const uint16_t* kc,
                                                    const uint16_t* vc, kv_geom kg, int layer, float* part, att_plan plan,
@@ -612,6 +626,12 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     const int cq = lane >> 4, lr = lane & 15;
     const int G = n_q / n_kv, QR = G * r.n;
     const int qbase = z * 16 * MQ;
+    // the slice's walk ends with the last position that one of its live rows attends
+    int pe = p1;
+    if (gridDim.z > 1) {
+        const int last = min(qbase + 16 * MQ, QR) - 1, i = last % r.n;
+        pe = min(p1, basepos + (last - i > qbase ? nlive : min(i + 1, nlive)));
+    }
     const int units = n_q + 2 * n_kv;                          // head units of a projection row
     const size_t RN = (size_t)r.B * r.n * units * D;           // elements of one split
 
@@ -640,10 +660,10 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
 #if ATT_INTERLEAVE
     // the four waves take the chunk's 32-position blocks in turn, so the
     // work-group reads K and V as two contiguous streams
-    const int wq0 = p0 + 32 * w, wq1 = p1, wstep = 128;
+    const int wq0 = p0 + 32 * w, wq1 = pe, wstep = 128;
 #else
-    const int wlen = ((p1 - p0 + 3) / 4 + 31) & ~31;               // positions per wave
-    const int wq0 = p0 + w * wlen, wq1 = min(wq0 + wlen, p1), wstep = 32;
+    const int wlen = ((pe - p0 + 3) / 4 + 31) & ~31;               // positions per wave
+    const int wq0 = p0 + w * wlen, wq1 = min(wq0 + wlen, pe), wstep = 32;
 #endif
     // K fragments of the two 16-position tiles and the V block of the block at
     // blk, through buffer resources limited to the cached positions: reads at
@@ -812,20 +832,20 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
 
     // two register sets: the next block's K and V load while this one computes
     u32x4 kf0[2][KS], kf1[2][KS], vv0[CPP / 2], vv1[CPP / 2];
-    // a wave whose first block holds no new row loads it during the pass below
-    const bool early = wq0 + 32 <= basepos;
+    // a wave whose first block is in the cache already loads it during the pass below
+    const bool early = qs.stored || wq0 + 32 <= basepos;
     if (early) load_kv(wq0, kf0, vv0);
     // one pass of the work-group over (a) its 16 MQ query rows, rotated,
     // scaled and rounded to bf16 into LDS (the V tiles' space, unused until the
-    // first block) and (b) its KV head's new rows [n0, p1), K rotated and V,
-    // stored to the cache.  A task is 4 columns and their RoPE partners D/2
+    // first block) and (b) its KV head's new rows [n0, pe), K rotated and V,
+    // stored to the cache unless they are there.  A task is 4 columns and their RoPE partners D/2
     // further; a thread's task loads go out together, so the pass costs a
     // memory round trip or two before the K/V stream starts.
     uint16_t* qst = &Vs[0][0];                                  // [16 MQ][D]
     static_assert(16 * MQ * D <= 4 * 32 * LDV, "query rows fit the V tiles");
     {
         constexpr int QG = D / 8;                               // 4-column groups of a half row
-        const int n0 = max(p0, basepos), nkv = max(p1 - n0, 0);
+        const int n0 = max(p0, basepos), nkv = qs.stored ? 0 : max(pe - n0, 0);
         // tasks: the tile's live query rows, then the new K/V rows, then the
         // tile's rows past QR (zeros, no loads), so the loading tasks come first
         const int nlr = max(min(16 * MQ, QR - qbase), 0);
@@ -1195,13 +1215,14 @@ void launch_rope_kv(const rows_t& r, const float* qkv, const float* P, int S, co
 {
     const int R = r.B * r.n, units = n_q + 2 * c.n_kv;
     const int upw = 512 / c.head_dim;                       // head units per work-group: 256 threads, one pair each
-    dim3 grid(R, (units + upw - 1) / upw);
+    const int first = q_out ? 0 : n_q;
+    dim3 grid(R, (units - first + upw - 1) / upw);
     if (c.kv_f32)
         k_rope_kv<float><<<grid, 256, 0, s>>>(r, qkv, P, S, rope, n_q, c.n_kv, c.head_dim, (float*)c.k, (float*)c.v,
-                                              c.g, layer, q_out, upw);
+                                              c.g, layer, q_out, first, upw);
     else
         k_rope_kv<uint16_t><<<grid, 256, 0, s>>>(r, qkv, P, S, rope, n_q, c.n_kv, c.head_dim, (uint16_t*)c.k,
-                                                 (uint16_t*)c.v, c.g, layer, q_out, upw);
+                                                 (uint16_t*)c.v, c.g, layer, q_out, first, upw);
 }
 
 att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32)
@@ -1220,6 +1241,7 @@ att_plan attention_plan(int B, int n, int n_q, int n_kv, int max_ctx, int kv_f32
     // 4.5 us against 10.0, 13 of 96-288 in a cache of 448 10.5 + 4.7 against 12.6)
     if (!kv_f32 && max_ctx <= ATT_FULL_CHUNK && p.max_items > B) p.max_items = B;
     p.whole = p.max_items == B;
+    p.kv_first = !kv_f32 && p.zs > ATT_KV_SLICES;
     p.in_order = p.whole && (B > PLAN_SEQS || (long long)B * n_kv * p.zs <= ATT_TARGET_WGS);
     return p;
 }
@@ -1284,7 +1306,13 @@ static void attn_d(const rows_t& r, const att_plan& pl, qkv_src qs, float* q, in
         launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, q, s);
         launch_ev(k_attn_partial<float, D>, dim3(c.n_kv, pl.max_items, pl.zs), dim3(256), s, ev0, ev1, r, (const float*)q, n_q,
                   c.n_kv, (const float*)c.k, (const float*)c.v, c.g, layer, part, pl, (float*)out);
-    } else if (c.g.bt) {
+        return;
+    }
+    if (pl.kv_first) {
+        launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, nullptr, s);
+        qs.stored = true;
+    }
+    if (c.g.bt) {
         attn_mfma_launch<D, true>(r, pl, qs, n_q, c, layer, part, out, out_t, s, ev0, ev1);
     } else {
         attn_mfma_launch<D, false>(r, pl, qs, n_q, c, layer, part, out, out_t, s, ev0, ev1);

@@ -21,6 +21,10 @@ pytestmark = pytest.mark.gpu
 
 # two query heads per KV head, a hidden size that keeps the oracle quick
 GQA_F32 = dict(synth.TINY, name="gqa-f32", n_kv=2)
+GQA_D64 = dict(GQA_F32, name="gqa-d64", dtype="bf16")
+GQA4 = dict(name="gqa4", n_layers=2, hidden=256, n_q=8, n_kv=2, head_dim=128, ffn=512, vocab=512, dtype="bf16",
+            rope_theta=500000.0, rms_eps=1e-5)
+LONG = dict(GQA4, name="gqa5-long", n_layers=2, hidden=512, n_q=40, n_kv=8)
 
 
 def prefill_against_oracle(cfg, lens, ctx0, page, tol, seed=57):
@@ -57,14 +61,17 @@ def prefill_against_oracle(cfg, lens, ctx0, page, tol, seed=57):
 
 @pytest.mark.parametrize("lens,ctx0", [([63, 64, 65, 0, 1], 300), ([700, 129, 1, 0, 513], 530), ([900], 0)],
                          ids=["edges", "rounds", "single"])
-@pytest.mark.parametrize("cfg,page,tol", [(synth.TINY, 0, 5e-3), (GQA_F32, 0, 5e-3), (GQA_F32, 32, 5e-3)],
-                         ids=["f32", "f32-gqa", "f32-gqa-paged"])
+@pytest.mark.parametrize("cfg,page,tol", [(synth.TINY, 0, 5e-3), (GQA_F32, 0, 5e-3), (GQA_F32, 32, 5e-3),
+                                          (GQA_D64, 0, 2e-2), (GQA_D64, 64, 2e-2), (GQA4, 0, 2e-2), (GQA4, 32, 2e-2)],
+                         ids=["f32", "f32-gqa", "f32-gqa-paged", "d64", "d64-paged", "d128", "d128-paged"])
 def test_sliced_prefill_matches_oracle(cfg, page, tol, lens, ctx0):
     say("sliced prefill", cfg["name"], page, lens, ctx0)
     prefill_against_oracle(cfg, lens, ctx0, page, tol)
 
 
-@pytest.mark.parametrize("cfg,gamma,tol", [(GQA_F32, 31, 5e-3), (GQA_F32, 32, 5e-3)], ids=["f32-64", "f32-66"])
+@pytest.mark.parametrize("cfg,gamma,tol", [(GQA_F32, 31, 5e-3), (GQA_F32, 32, 5e-3), (GQA4, 15, 2e-2), (GQA4, 16, 2e-2),
+                                           (GQA4, 31, 2e-2), (GQA4, 32, 2e-2)],
+                         ids=["f32-64", "f32-66", "d128-64", "d128-68", "d128-128", "d128-132"])
 def test_long_draft_verify_matches_oracle(cfg, gamma, tol):
     say("long draft verify", cfg["name"], gamma)
     verify_against_oracle([0, 300, 611], 700, gamma, 0, tol=tol, cfg=cfg)
@@ -97,7 +104,7 @@ def piece_ratio(cfg, n, pieces):
     return r
 
 
-@pytest.mark.parametrize("cfg,n,pieces", [(synth.TINY, 1000, 4)], ids=["f32"])
+@pytest.mark.parametrize("cfg,n,pieces", [(synth.TINY, 1000, 4), (LONG, 2500, 8)], ids=["f32", "bf16"])
 def test_a_prompt_in_one_round_takes_no_longer_than_in_pieces(cfg, n, pieces):
     r = piece_ratio(cfg, n, pieces)
     say("one round against", pieces, "pieces:", round(r, 3))
