@@ -913,12 +913,19 @@ int launch_gemm_bf16_swiglu(const uint16_t* A, const uint16_t* W, void* out, act
     return 1;
 }
 
+// Rows up to which the row kernel's passes of 4 or 8 rows over the weights (which
+// the caches hold) are the faster ones on every decoder measured: verify of 64,
+// 128, 192 and 256 rows 102, 134, 165 and 197 us at hidden 256 (two layers), 150,
+// 250, 354 and 458 at hidden 1024 (one), 1840, 3600, 5370 and 7130 at hidden 4096
+// (one), in tiles 590, 597, 601 and 601; 1140, 1155, 1165 and 1172; 4930, 5100,
+// 5490 and 5730.
+constexpr int F32_ROWS = 192;
+
 void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int ldc, gemm_mode mode,
                      hipStream_t s)
 {
-    // few rows: passes of 4 or 8 over the weights (which the caches hold); the tiles where a pass per 8 rows is more
     if (M <= 4) k_gemm_f32_rows<4><<<dim3(N / 8, 1), 256, 0, s>>>(A, W, C, M, N, K, ldc, mode);
-    else if (M <= 64) k_gemm_f32_rows<8><<<dim3(N / 8, (M + 7) / 8), 256, 0, s>>>(A, W, C, M, N, K, ldc, mode);
+    else if (M <= F32_ROWS) k_gemm_f32_rows<8><<<dim3(N / 8, (M + 7) / 8), 256, 0, s>>>(A, W, C, M, N, K, ldc, mode);
     else k_gemm_f32<<<dim3(N / FT, (M + FT - 1) / FT), 256, 0, s>>>(A, W, C, M, N, K, ldc, mode);
 }
 

@@ -1,6 +1,6 @@
 """The fp32 decoder's few-row GEMMs (k_gemm_f32_rows, k_gemm_q4_f32) and the
-tiled one past 64 rows, against the oracle: one SD step whose drafts have 1 to
-14 rows and whose verify has 5 to 70, on a decoder with 3 and 5 groups along K
+tiled one past 192 rows, against the oracle: one SD step whose drafts have 1 to
+39 rows and whose verify has 5 to 195, on a decoder with 3 and 5 groups along K
 (waves without a group, lanes without a last piece), in every drafter format."""
 import pytest
 
@@ -15,7 +15,7 @@ CFG = dict(name="f32-rows", n_layers=1, hidden=384, n_q=6, n_kv=2, head_dim=64, 
 
 
 @pytest.mark.parametrize("fmt", ["w4", "w4a", "w8"])
-@pytest.mark.parametrize("B", [1, 4, 5, 9, 14])
+@pytest.mark.parametrize("B", [1, 4, 5, 9, 14, 38, 39])
 def test_few_row_gemms_match_oracle(B, fmt):
     say("f32 rows", B, fmt)
     W = synth.make_weights(CFG, 3, "cpu", std=0.05)
