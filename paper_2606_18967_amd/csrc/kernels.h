@@ -123,13 +123,12 @@ void launch_kv_poison(int B, const int32_t* slots, const int32_t* kv_len, int sp
 
 // ---- GEMMs (kernels_gemm.hip): C[M][N] (fp32, row stride ldc) = or += A[M][K] W^T
 enum gemm_mode : int { GEMM_STORE = 0, GEMM_ADD = 1 };
-// bf16 MFMA GEMM: weight-streaming kernel for M <= 64 per m-tile, LDS-tiled
-// kernel for M > 64.  part is split-K scratch of part_cap floats (no split
-// when too small).  Returns the number of K splits S used.  With
+// bf16 MFMA GEMM: DMA-fed tiles where N is a multiple of 128, a weight-streaming
+// kernel at other multiples of 64.  part is split-K scratch of part_cap floats
+// (no split when too small).  Returns the number of K splits S used.  With
 // defer_reduce and S > 1 the partials are left in part ([S][M][N]) for the
-// consumer to sum; otherwise C holds the result.  lds_dma: 320-row tiles
-// without split-K use the DMA-fed kernel (same sums as the register-staged
-// one; false selects the latter).  live (device): row tiles past *live are
+// consumer to sum; otherwise C holds the result.  lds_dma = false puts the
+// register-staged kernel in the place of the 320-row tiles (same sums).  live (device): row tiles past *live are
 // skipped (rows_t).
 int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part, size_t part_cap, int M, int N, int K,
                      int ldc, gemm_mode mode, bool defer_reduce, hipStream_t s, bool lds_dma = true,

@@ -1,10 +1,10 @@
 // kernels_gemm.hip -- the bf16 projections: C[M][N] (fp32) = or += A[M][K] W^T.
 //
 // Weights are row-major [N][K] (K contiguous), activations [M][K].
-//   - gemm_dma (N a multiple of 256, beyond 64 rows of 128): tiles of 64 to
-//     320 rows, both operands brought into LDS by DMA; see k_gemm_dma.
-//   - gemm_stream (other N): weights streamed from HBM into registers,
-//     v_mfma_f32_16x16x32_bf16; see k_gemm_stream.
+//   - gemm_dma (N a multiple of 128): tiles of 64 to 320 rows, both operands
+//     brought into LDS by DMA; see k_gemm_dma.
+//   - gemm_stream (N an odd multiple of 64): weights streamed from HBM into
+//     registers, v_mfma_f32_16x16x32_bf16; see k_gemm_stream.
 //   - gemm_f32 / gemm_q4_f32: plain VALU versions for fp32 models (the int4
 //     one reads the packed layout of kernels_q4.hip).
 #include "common.h"
@@ -100,12 +100,11 @@ __global__ void __launch_bounds__(256) k_gemm_f32_rows(const float* __restrict__
 __device__ __forceinline__ float f16_bits_to_f32(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 
 // ------------------------------------------------------------------ weight-streaming bf16 MFMA GEMM
-// C[M][N] = A[M][K] W^T for decode-shaped M (up to 64 rows per m-tile; the
-// AR step and the draft LM head).  A work-group covers a 64-row m-tile,
-// 64*NBW columns (NBW 16-column blocks per wave, 4 waves) and a range of K
-// split into chunks of 128.  The A chunk is staged in LDS (double-buffered)
-// and shared by the four waves; each wave streams its weight columns from
-// HBM straight into registers through a ring of RD register sets (RD - 1
+// C[M][N] = A[M][K] W^T where N is an odd multiple of 64 (an LM head of such a
+// vocabulary).  A work-group covers a 64-row m-tile, 64 columns (16 per wave, 4
+// waves) and a range of K split into chunks of 128.  The A chunk is staged in LDS
+// (double-buffered) and shared by the four waves; each wave streams its weight
+// columns from HBM straight into registers through a ring of RD register sets (RD - 1
 // chunks in flight), so every weight byte is read once per m-tile.  Lane l
 // covers k = 128g + 32j + 8(l/16) + 0..7 of chunk g in k-step j
 // (v_mfma_f32_16x16x32_bf16): each load instruction reads 64 contiguous
@@ -117,12 +116,12 @@ constexpr int SK = 128;          // k per chunk
 constexpr int ALD = SK + 8;      // LDS row stride in 2-byte elements
 constexpr int SM = 64;           // rows per m-tile
 
-template <int NBW, int MT, int NW>
-__global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wt,
+template <int MT>
+__global__ void __launch_bounds__(256) k_gemm_stream(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wt,
                                                      float* __restrict__ C, float* __restrict__ P, int M, int N, int K,
                                                      int ldc, int mode, int S, int msup, int total)
 {
-    constexpr int RD = NW == 8 ? 4 : 3;   // register sets in the load ring (deeper where the registers allow)
+    constexpr int RD = 3;                                   // register sets in the load ring
     __shared__ __attribute__((aligned(16))) uint16_t As[2][SM * ALD];
     const int per_xcd = gridDim.x >> 3;                     // gridDim.x is a multiple of 8
     const int w = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -132,7 +131,7 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restr
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m0 = ms * SM;
     const int G = K / SK, Gs = G / S, g0 = s * Gs, g1 = g0 + Gs;
-    const int nb0 = (tile * NW + wv) * NBW;
+    const int nb = tile * 4 + wv;                           // this wave's 16-column block
     const int rows = min(M - m0, MT * 16);                  // rows staged (others stay zero)
     // each work item walks its chunks from a different starting offset: in
     // lockstep they would all read the same 256-byte column of the weight
@@ -143,12 +142,12 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restr
     // A tiles travel through a ring of register sets too (same depth as the
     // weights): the tile of chunk c + 1 is requested RD - 2 chunks before it
     // is stored to LDS
-    constexpr int AP = 1024 / (64 * NW);                  // 16-byte A pieces per thread per chunk
+    constexpr int AP = 4;                                 // 16-byte A pieces per thread per chunk
     u32x4 ar[RD][AP];
     auto load_a = [&](int g, u32x4 (&a)[AP]) {
 #pragma unroll
         for (int t = 0; t < AP; ++t) {
-            const int pidx = tid + t * 64 * NW;
+            const int pidx = tid + t * 256;
             const int row = pidx >> 4, col = (pidx & 15) * 8;
             a[t] = *(const u32x4*)(A + (size_t)(m0 + min(row, rows - 1)) * K + (size_t)phys(g) * SK + col);
         }
@@ -158,43 +157,32 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restr
     auto store_a = [&](int buf, const u32x4 (&a)[AP], bool valid) {
 #pragma unroll
         for (int t = 0; t < AP; ++t) {
-            const int pidx = tid + t * 64 * NW;
+            const int pidx = tid + t * 256;
             const int row = pidx >> 4, col = (pidx & 15) * 8;
             if (row < MT * 16)
                 *(u32x4*)(&As[buf][row * ALD + col]) = (valid && row < rows) ? a[t] : (u32x4){0u, 0u, 0u, 0u};
         }
     };
-    u32x4 wr[RD][NBW][4];
-    auto load_w = [&](int g, u32x4 (&wq)[NBW][4]) {
+    u32x4 wr[RD][4];
+    auto load_w = [&](int g, u32x4 (&wq)[4]) {
+        const uint16_t* wp = Wt + (size_t)(nb * 16 + (lane & 15)) * K + (size_t)phys(g) * SK + 8 * (lane >> 4);
 #pragma unroll
-        for (int i = 0; i < NBW; ++i) {
-            const uint16_t* wp = Wt + (size_t)((nb0 + i) * 16 + (lane & 15)) * K + (size_t)phys(g) * SK + 8 * (lane >> 4);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wq[i][j] = *(const u32x4*)(wp + 32 * j);   // j, j + 1 share a 128-byte line: cached
-        }
+        for (int j = 0; j < 4; ++j) wq[j] = *(const u32x4*)(wp + 32 * j);   // j, j + 1 share a 128-byte line: cached
     };
 
-    floatx4 acc[NBW][MT];
+    floatx4 acc[MT];
 #pragma unroll
-    for (int i = 0; i < NBW; ++i)
-#pragma unroll
-        for (int t = 0; t < MT; ++t) acc[i][t] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < MT; ++t) acc[t] = (floatx4){0.f, 0.f, 0.f, 0.f};
 
-    auto compute = [&](int buf, const u32x4 (&wq)[NBW][4]) {
+    auto compute = [&](int buf, const u32x4 (&wq)[4]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint16_t* ab = &As[buf][(lane & 15) * ALD + 32 * j + 8 * (lane >> 4)];
-            u32x4 af[MT];
+            const bf16x8 bb = __builtin_bit_cast(bf16x8, wq[j]);
 #pragma unroll
-            for (int t = 0; t < MT; ++t) af[t] = *(const u32x4*)(ab + t * 16 * ALD);
-#pragma unroll
-            for (int i = 0; i < NBW; ++i) {
-                const bf16x8 bb = __builtin_bit_cast(bf16x8, wq[i][j]);
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-                    acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[t]), bb,
-                                                                       acc[i][t], 0, 0, 0);
-            }
+            for (int t = 0; t < MT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, *(const u32x4*)(ab + t * 16 * ALD)), bb, acc[t], 0, 0, 0);
         }
     };
 
@@ -231,23 +219,20 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_stream(const uint16_t* __restr
     }
 
     // ---- epilogue
+    const int col = nb * 16 + (lane & 15);
 #pragma unroll
-    for (int i = 0; i < NBW; ++i) {
-        const int col = (nb0 + i) * 16 + (lane & 15);
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + t * 16 + (lane >> 4) * 4 + r;
-                if (row >= M) continue;
-                if (S == 1) {
-                    float* cp = C + (size_t)row * ldc + col;
-                    *cp = mode == GEMM_ADD ? *cp + acc[i][t][r] : acc[i][t][r];
-                } else {
-                    P[((size_t)s * M + row) * N + col] = acc[i][t][r];
-                }
+        for (int r = 0; r < 4; ++r) {
+            const int row = m0 + t * 16 + (lane >> 4) * 4 + r;
+            if (row >= M) continue;
+            if (S == 1) {
+                float* cp = C + (size_t)row * ldc + col;
+                *cp = mode == GEMM_ADD ? *cp + acc[t][r] : acc[t][r];
+            } else {
+                P[((size_t)s * M + row) * N + col] = acc[t][r];
             }
-    }
+        }
 }
 
 // ------------------------------------------------------------------ tiled bf16 MFMA GEMM, register-staged
@@ -712,8 +697,9 @@ __global__ void __launch_bounds__(256) k_gemm_q4_f32(const float* __restrict__ A
 
 }  // namespace
 
-// Split-K is used until the launch has GEMM_SPLIT_TARGET work-groups, with at
-// most GEMM_MAX_SPLIT splits and at least two chunks per split.
+// K splits of the weight-streaming kernel: doubled until the launch has
+// GEMM_SPLIT_TARGET work-groups, with at most GEMM_MAX_SPLIT splits and at least
+// two chunks per split.
 #ifndef GEMM_SPLIT_TARGET
 #define GEMM_SPLIT_TARGET 256
 #endif
@@ -721,16 +707,13 @@ __global__ void __launch_bounds__(256) k_gemm_q4_f32(const float* __restrict__ A
 #define GEMM_MAX_SPLIT 8
 #endif
 
-void gemm_plan(int M, int N, int K, int* nbw, int* S)
+static int stream_splits(int M, int N, int K)
 {
-    *nbw = (N % 128 == 0) ? 2 : 1;
-    int tiles = N / (64 * *nbw);
-    int msup = (M + SM - 1) / SM;
-    int G = K / SK;
+    const int tiles = N / 64, msup = (M + SM - 1) / SM, G = K / SK;
     int s = 1;
     while (tiles * s * msup < GEMM_SPLIT_TARGET && G % (2 * s) == 0 && G / (2 * s) >= 2 && 2 * s <= GEMM_MAX_SPLIT)
         s *= 2;
-    *S = s;
+    return s;
 }
 
 // The DMA-fed tiles' plan: tile height 32 mt, width 64 wcn, S splits of the
@@ -785,9 +768,7 @@ static dma_tile dma_plan(int M, int N, int K)
 
 size_t gemm_part_floats(int M, int N, int K)
 {
-    int nbw, S;
-    gemm_plan(M, N, K, &nbw, &S);
-    if (use_dma(N, K)) S = dma_plan(M, N, K).S;
+    const int S = use_dma(N, K) ? dma_plan(M, N, K).S : stream_splits(M, N, K);
     return S > 1 ? (size_t)S * M * N : 0;
 }
 
@@ -839,19 +820,6 @@ static void dma_launch(const dma_args& a, dma_tile p, hipStream_t s)
     }
 }
 
-template <int NBW, int NW>
-static void stream_mt(int MT, dim3 grid, hipStream_t s, const uint16_t* A, const uint16_t* W, float* C, float* P, int M,
-                      int N, int K, int ldc, int mode, int S, int msup, int total)
-{
-    constexpr int T = 64 * NW;
-    switch (MT) {
-        case 1: k_gemm_stream<NBW, 1, NW><<<grid, T, 0, s>>>(A, W, C, P, M, N, K, ldc, mode, S, msup, total); break;
-        case 2: k_gemm_stream<NBW, 2, NW><<<grid, T, 0, s>>>(A, W, C, P, M, N, K, ldc, mode, S, msup, total); break;
-        case 3: k_gemm_stream<NBW, 3, NW><<<grid, T, 0, s>>>(A, W, C, P, M, N, K, ldc, mode, S, msup, total); break;
-        default: k_gemm_stream<NBW, 4, NW><<<grid, T, 0, s>>>(A, W, C, P, M, N, K, ldc, mode, S, msup, total); break;
-    }
-}
-
 static void reduce_splits(const float* part, float* C, int M, int N, int ldc, int S, int mode, hipStream_t s)
 {
     const size_t MN = (size_t)M * N;
@@ -874,21 +842,18 @@ int launch_gemm_bf16(const uint16_t* A, const uint16_t* W, float* C, float* part
         if (p.S > 1 && !defer_reduce) reduce_splits(part, C, M, N, ldc, p.S, mode, s);
         return p.S;
     }
-    int nbw, S;
-    gemm_plan(M, N, K, &nbw, &S);
+    int S = stream_splits(M, N, K);
     if (S > 1 && (size_t)S * M * N > part_cap) S = 1;   // workspace too small: no split
-    int msup = (M + SM - 1) / SM;
-    int MT = msup > 1 ? 4 : (M + 15) / 16;
-    // 8-wave work-groups (twice the columns, one A tile for twice the waves)
-    // when 4-wave ones would not all be resident at once (two per CU): the
-    // draft LM head then runs in a single wave of work-groups
-    const bool wide = nbw == 2 && N % 256 == 0 && (N / 128) * S * msup > 512;
-    int tiles = N / (64 * nbw * (wide ? 2 : 1));
-    int total = tiles * S * msup;
-    dim3 grid((total + 7) / 8 * 8);
-    if (wide) stream_mt<2, 8>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
-    else if (nbw == 2) stream_mt<2, 4>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
-    else stream_mt<1, 4>(MT, grid, s, A, W, C, part, M, N, K, ldc, mode, S, msup, total);
+    const int msup = (M + SM - 1) / SM, total = N / 64 * S * msup;
+    auto go = [&](auto kern) {
+        kern<<<dim3((total + 7) / 8 * 8), 256, 0, s>>>(A, W, C, part, M, N, K, ldc, mode, S, msup, total);
+    };
+    switch (msup > 1 ? 4 : (M + 15) / 16) {
+        case 1: go(k_gemm_stream<1>); break;
+        case 2: go(k_gemm_stream<2>); break;
+        case 3: go(k_gemm_stream<3>); break;
+        default: go(k_gemm_stream<4>); break;
+    }
     if (S > 1 && !defer_reduce) reduce_splits(part, C, M, N, ldc, S, mode, s);
     return S;
 }
