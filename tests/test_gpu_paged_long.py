@@ -22,7 +22,7 @@ import oracle
 from paper_2606_18967_amd import sdrl, synth
 
 from gpu_common import DeviceKV, host_bits, i32, oracle_kv_from_device, oracle_models, say
-from test_gpu_attention_chunks import _chunk_bounds
+from test_gpu_attention_plan import chunks
 
 pytestmark = pytest.mark.gpu
 
@@ -41,8 +41,9 @@ def test_paged_verify_past_the_page_window_matches_dense_and_oracle(cfg):
     # ragged: most contexts past the window of every wave, a few short ones
     lens = [3000 + 7 * b if b % 16 == 5 else 16500 + (53 * b) % 190 for b in range(B)]
     max_ctx = max(lens) + gamma + 8
-    assert all(not _chunk_bounds(cfg, B, gamma + 1, max_ctx, kl + gamma + 1) for kl in lens)   # one chunk each
-    clen = [((kl + gamma + 1) + 31) & ~31 for kl in lens]
+    ctx = [kl + gamma + 1 for kl in lens]
+    clen = chunks(ctx, cfg["n_kv"])
+    assert all(c >= x for c, x in zip(clen, ctx))                     # one chunk each
     assert sum(c > 96 + 32 * 4 * WINDOW for c in clen) >= B - 4     # wave 3 of these reaches block 128
     say("paged verify past the page window", B, min(lens), max(lens))
     W = [w.cuda() for w in synth.make_weights(cfg, seed, "cpu")]
