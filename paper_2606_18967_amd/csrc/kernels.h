@@ -98,7 +98,6 @@ struct qkv_src {
     const float* P;
     int S;
     const float2* rope;
-    bool stored = false;     // the new K/V rows are in the cache (att_plan::kv_first)
 };
 // ev0/ev1, when given, are bound to the attention kernel's own dispatch
 // (hipExtLaunchKernelGGL): their elapsed time is the kernel's run time.

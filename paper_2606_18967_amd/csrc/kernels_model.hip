@@ -577,7 +577,7 @@ __global__ void __launch_bounds__(256) k_attn_partial(rows_t r, const float* q, 
 // its context range to the cache before its waves read them (each
 // work-group of the head covering new positions writes those it reads; two
 // query-row slices of one chunk write the same values, and with more of them
-// k_rope_kv has stored the rows before, qs.stored), and it raises the slot,
+// k_rope_kv has stored the rows before, plan.kv_first), and it raises the slot,
 // position and page flags for them.  A slice's walk ends at the last position
 // that its rows attend.
 template <int D, int MQ, bool PAGED>
@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     const int qbase = z * 16 * MQ;
     // the slice's walk ends with the last position that one of its live rows attends
     int pe = p1;
-    if (gridDim.z > 1) {
+    if (plan.zs > 1) {
         const int last = min(qbase + 16 * MQ, QR) - 1, i = last % r.n;
         pe = min(p1, basepos + (last - i > qbase ? nlive : min(i + 1, nlive)));
     }
@@ -833,7 +833,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     // two register sets: the next block's K and V load while this one computes
     u32x4 kf0[2][KS], kf1[2][KS], vv0[CPP / 2], vv1[CPP / 2];
     // a wave whose first block is in the cache already loads it during the pass below
-    const bool early = qs.stored || wq0 + 32 <= basepos;
+    const bool early = plan.kv_first || wq0 + 32 <= basepos;
     if (early) load_kv(wq0, kf0, vv0);
     // one pass of the work-group over (a) its 16 MQ query rows, rotated,
     // scaled and rounded to bf16 into LDS (the V tiles' space, unused until the
@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(256, MQ <= 2 ? 2 : 1) k_attn_mfma(rows_t r, in
     static_assert(16 * MQ * D <= 4 * 32 * LDV, "query rows fit the V tiles");
     {
         constexpr int QG = D / 8;                               // 4-column groups of a half row
-        const int n0 = max(p0, basepos), nkv = qs.stored ? 0 : max(pe - n0, 0);
+        const int n0 = max(p0, basepos), nkv = plan.kv_first ? 0 : max(pe - n0, 0);
         // tasks: the tile's live query rows, then the new K/V rows, then the
         // tile's rows past QR (zeros, no loads), so the loading tasks come first
         const int nlr = max(min(16 * MQ, QR - qbase), 0);
@@ -1308,10 +1308,7 @@ static void attn_d(const rows_t& r, const att_plan& pl, qkv_src qs, float* q, in
                   c.n_kv, (const float*)c.k, (const float*)c.v, c.g, layer, part, pl, (float*)out);
         return;
     }
-    if (pl.kv_first) {
-        launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, nullptr, s);
-        qs.stored = true;
-    }
+    if (pl.kv_first) launch_rope_kv(r, qs.qkv, qs.P, qs.S, qs.rope, n_q, c, layer, nullptr, s);
     if (c.g.bt) {
         attn_mfma_launch<D, true>(r, pl, qs, n_q, c, layer, part, out, out_t, s, ev0, ev1);
     } else {
