@@ -8,7 +8,6 @@
 
 #include <limits.h>
 
-#include <iterator>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -247,42 +246,47 @@ static size_t prefill_gpart_bytes(const sd_model_cfg& c, int rows)
     return mx * 4;
 }
 
-struct ws_block { void** p; size_t bytes; };
+// Buffers to allocate, in a fixed list (no C++ exception can leave a C entry).
+struct ws_blocks_t {
+    struct { void** p; size_t bytes; } b[16];
+    int n = 0;
+    template <typename T>
+    void add(T** p, size_t bytes) { b[n++] = {(void**)p, bytes}; }
+};
 
 // A prefill's buffers hold the target's activations only (bf16 ones in two
 // bytes), and no gate/up: its SwiGLU is fused or reads the split partials.
-static std::vector<ws_block> ws_blocks(const sd_model_cfg& c, int max_slots, bool prefill, workspace& w)
+static ws_blocks_t ws_blocks(const sd_model_cfg& c, int max_slots, bool prefill, workspace& w)
 {
     const size_t R = (size_t)w.rows, qkvN = (size_t)(c.n_q + 2 * c.n_kv) * c.head_dim, qd = (size_t)c.n_q * c.head_dim;
     const bool f32 = c.dtype == SD_DTYPE_F32;
     const size_t el = prefill && !f32 ? 2 : 4;
     const size_t gp = prefill ? prefill_gpart_bytes(c, w.rows) : gpart_bytes(c, w.rows, max_slots);
     w.gpart_cap = gp / 4;
-    std::vector<ws_block> b = {
-        {(void**)&w.h, R * c.hidden * 4},
-        {(void**)&w.a, R * c.hidden * el},
-        {(void**)&w.qkv, R * qkvN * 4},
-        {(void**)&w.att, R * qd * el},
-        {(void**)&w.act, R * c.ffn * el},
-        {(void**)&w.att_part, attention_part_floats(w.rows, c.n_q, c.n_kv, c.head_dim, f32) * 4},
-        {(void**)&w.gpart, gp},
-    };
-    if (f32) b.push_back({(void**)&w.qrot, R * qd * 4});
-    if (!prefill || f32) b.push_back({(void**)&w.gu, R * 2 * (size_t)c.ffn * 4});
-    return b;
+    ws_blocks_t l;
+    l.add(&w.h, R * c.hidden * 4);
+    l.add(&w.a, R * c.hidden * el);
+    l.add(&w.qkv, R * qkvN * 4);
+    l.add(&w.att, R * qd * el);
+    l.add(&w.act, R * c.ffn * el);
+    l.add(&w.att_part, attention_part_floats(w.rows, c.n_q, c.n_kv, c.head_dim, f32) * 4);
+    l.add(&w.gpart, gp);
+    if (f32) l.add(&w.qrot, R * qd * 4);
+    if (!prefill || f32) l.add(&w.gu, R * 2 * (size_t)c.ffn * 4);
+    return l;
 }
 
 // All of the blocks or none; the failed one's bytes, or 0.
-static size_t alloc_blocks(const std::vector<ws_block>& b)
+static size_t alloc_blocks(const ws_blocks_t& l)
 {
-    for (size_t i = 0; i < b.size(); ++i) {
-        if (hipMalloc(b[i].p, b[i].bytes) == hipSuccess) continue;
+    for (int i = 0; i < l.n; ++i) {
+        if (hipMalloc(l.b[i].p, l.b[i].bytes) == hipSuccess) continue;
         (void)hipGetLastError();
-        for (size_t k = 0; k <= i; ++k) {
-            if (k < i) (void)hipFree(*b[k].p);
-            *b[k].p = nullptr;
+        for (int k = 0; k <= i; ++k) {
+            if (k < i) (void)hipFree(*l.b[k].p);
+            *l.b[k].p = nullptr;
         }
-        return b[i].bytes;
+        return l.b[i].bytes;
     }
     return 0;
 }
@@ -328,9 +332,9 @@ static workspace& prefill_ws(sd_engine e, long long rows, hipStream_t s)
     }
     workspace w;
     w.rows = PREFILL_ROWS;
-    const std::vector<ws_block> blocks = ws_blocks(e->c, e->max_slots, true, w);
+    const ws_blocks_t blocks = ws_blocks(e->c, e->max_slots, true, w);
     size_t need = 0, avail = 0, total = 0;
-    for (const ws_block& b : blocks) need += b.bytes;
+    for (int i = 0; i < blocks.n; ++i) need += blocks.b[i].bytes;
     if (hipMemGetInfo(&avail, &total) != hipSuccess) (void)hipGetLastError();
     else if (need <= avail / 4 && !alloc_blocks(blocks)) e->pf = w;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
@@ -359,16 +363,13 @@ extern "C" sd_status sd_create(const sd_model_cfg* cfg, int32_t max_slots, int32
     if (hipGetDevice(&e->dev) != hipSuccess) { delete e; return fail(SD_E_HIP, "hipGetDevice failed"); }
 
     const sd_model_cfg& c = *cfg;
-    std::vector<ws_block> blocks = ws_blocks(c, max_slots, false, e->ws);
-    const ws_block more[] = {
-        {(void**)&e->plan, attention_plan_bytes(max_slots, c.n_kv)},
-        {(void**)&e->samp_part, sample_part_floats(e->ws.rows, c.vocab) * 4},
-        {(void**)&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4},
-        {(void**)&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2)},
-        {(void**)&e->err, ERR_COUNT * 4},
-        {(void**)&e->pf_lim, ((size_t)2 * max_slots + 1) * 4},
-    };
-    blocks.insert(blocks.end(), std::begin(more), std::end(more));
+    ws_blocks_t blocks = ws_blocks(c, max_slots, false, e->ws);
+    blocks.add(&e->plan, attention_plan_bytes(max_slots, c.n_kv));
+    blocks.add(&e->samp_part, sample_part_floats(e->ws.rows, c.vocab) * 4);
+    blocks.add(&e->acc_work, accept_work_floats(max_slots, max_gamma) * 4);
+    blocks.add(&e->rope, (size_t)max_ctx * (c.head_dim / 2) * sizeof(float2));
+    blocks.add(&e->err, ERR_COUNT * 4);
+    blocks.add(&e->pf_lim, ((size_t)2 * max_slots + 1) * 4);
     if (const size_t failed = alloc_blocks(blocks)) {
         delete e;
         return fail(SD_E_NOMEM, "workspace allocation of %zu bytes failed", failed);
