@@ -122,19 +122,26 @@ def measured_traffic(kind: str, workload: str = DEFAULT_WORKLOAD):
     return d.get("bytes")
 
 
-# the kernel each timing class brackets (bf16 KV cache, head_dim 128, M = 64 drafter rows, 320 verify rows)
+# the kernels each timing class brackets (bf16 KV cache, head_dim 128, M = 64 drafter rows, 320 verify rows)
 KERNEL_OF_CLASS = {
     "attn_decode": "k_attn_mfma<128, 1, false>",
     "attn_verify": "k_attn_mfma<128, 2, false>",
-    "int4_proj": "k_gemm_q4<2, 0, false> (qkv, o, down; gate/up runs unsplit as the SwiGLU variant <2, 0, true> "
-                 "where N allows)",
-    "bf16_proj": "k_gemm_dma<10, 2, 4, 2, false> (qkv, o, down; gate/up runs as the SwiGLU variant where N allows)",
-    "lm_head": "k_gemm_dma<2, 2, 4, 3, false> (draft rows), k_gemm_dma<10, 2, 4, 2, false> (verify rows)",
+    "int4_proj": "k_gemm_q4<2, 0, false> (qkv, o, down), k_gemm_q4<2, 0, true> (gate/up with SwiGLU)",
+    "bf16_proj": "k_gemm_dma<10, 2, 2, 2, false, false> (qkv, o), k_gemm_dma<10, 2, 4, 2, false, false> (down), "
+                 "k_gemm_dma<10, 2, 4, 2, true, false> (gate/up with SwiGLU)",
+    "lm_head": "k_gemm_dma<2, 2, 4, 3, false, false> (draft rows), k_gemm_dma<10, 2, 4, 2, false, false> (verify rows)",
 }
-# the counter ingest keeps, per class, only the dispatches of its kernel
-# launched by that class (work-group counts tell the verify LM head, 594
-# 320x256 tiles at V = 152064, from the split projections, <= 240)
-CLASS_WG_FILTER = {"bf16_proj": lambda wgs: wgs < 500, "lm_head": lambda wgs: wgs >= 500}
+# their dispatches in a counter run: instance and which work-group counts are the class's (they tell an LM head, 594
+# tiles of 256 columns at V = 152064, from the projections that run as the same instance, <= 240)
+COUNTED = {
+    "attn_decode": {"k_attn_mfma<128,1,false>": None},
+    "attn_verify": {"k_attn_mfma<128,2,false>": None},
+    "int4_proj": {"k_gemm_q4<2,0,false>": None, "k_gemm_q4<2,0,true>": None},
+    "bf16_proj": {"k_gemm_dma<10,2,2,2,false,false>": None, "k_gemm_dma<10,2,4,2,false,false>": lambda wgs: wgs < 500,
+                  "k_gemm_dma<10,2,4,2,true,false>": None},
+    "lm_head": {"k_gemm_dma<2,2,4,3,false,false>": lambda wgs: wgs >= 500,
+                "k_gemm_dma<10,2,4,2,false,false>": lambda wgs: wgs >= 500},
+}
 
 
 # bytes per quantized weight: codes + fp16 scale (+ zero point) per group of 128
@@ -196,45 +203,45 @@ def kernel_key(name):
 def ingest_pmc(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, out_path):
     """Writes profiles/traffic.json from rocprofv3 --pmc counter_collection.csv
     files: the bench run's FETCH_SIZE and WRITE_SIZE (KiB per dispatch)
-    averaged per kernel, scaled by what the same counters read for the
-    COPY_BYTES copy (the kernel with the largest reading in the copy runs)."""
+    averaged over a class's dispatches, scaled by what the same counters read
+    for the COPY_BYTES copy (the kernel with the largest reading in the copy
+    runs)."""
     import csv
 
-    def per_kernel(path, counter, keep=None):
+    def dispatches(path, counter):
+        """{dispatch: [kernel, work-groups, reading]}"""
         acc = {}
         with open(path) as fh:
             for row in csv.DictReader(fh):
                 if row.get("Counter_Name") != counter:
                     continue
-                k = kernel_key(row["Kernel_Name"])
                 wgs = int(row.get("Grid_Size", 0)) // max(1, int(row.get("Workgroup_Size", 1)))
-                if keep and k in keep and not keep[k](wgs):
-                    continue
-                d = row.get("Dispatch_Id") or row.get("Correlation_Id")
-                acc.setdefault(k, {})
-                acc[k][d] = acc[k].get(d, 0.0) + float(row["Counter_Value"])
-        return {k: (sum(v.values()) / len(v), len(v)) for k, v in acc.items()}
+                d = acc.setdefault(row.get("Dispatch_Id") or row.get("Correlation_Id"),
+                                   [kernel_key(row["Kernel_Name"]), wgs, 0.0])
+                d[2] += float(row["Counter_Value"])
+        return list(acc.values())
 
     def copy_factor(path, counter):
-        name, (kib, _) = max(per_kernel(path, counter).items(), key=lambda kv: kv[1][0])
+        per = {}
+        for k, _, kib in dispatches(path, counter):
+            per.setdefault(k, []).append(kib)
+        name, kib = max(((k, sum(v) / len(v)) for k, v in per.items()), key=lambda kv: kv[1])
         return COPY_BYTES / (kib * 1024.0), name, kib
+
+    def mean_bytes(rows, counted, factor):
+        kib = [x for k, wgs, x in rows if k in counted and (counted[k] is None or counted[k](wgs))]
+        return sum(kib) / len(kib) * 1024 * factor if kib else None, len(kib)
 
     ff, fname, fkib = copy_factor(copy_fetch_csv, "FETCH_SIZE")
     wf, wname, wkib = copy_factor(copy_write_csv, "WRITE_SIZE")
-    fetch = {c: per_kernel(fetch_csv, "FETCH_SIZE", {kernel_key(KERNEL_OF_CLASS[c]): f})
-             for c, f in CLASS_WG_FILTER.items()}
-    write = {c: per_kernel(write_csv, "WRITE_SIZE", {kernel_key(KERNEL_OF_CLASS[c]): f})
-             for c, f in CLASS_WG_FILTER.items()}
-    fetch_all = per_kernel(fetch_csv, "FETCH_SIZE")
-    write_all = per_kernel(write_csv, "WRITE_SIZE")
+    fetch, write = dispatches(fetch_csv, "FETCH_SIZE"), dispatches(write_csv, "WRITE_SIZE")
     per = {}
-    for cls, kname in KERNEL_OF_CLASS.items():
-        k = kernel_key(kname)
-        fe, wr = (fetch[cls], write[cls]) if cls in CLASS_WG_FILTER else (fetch_all, write_all)
-        if k not in fe or k not in wr:
+    for cls, counted in COUNTED.items():
+        fb, n = mean_bytes(fetch, counted, ff)
+        wb, m = mean_bytes(write, counted, wf)
+        if not n or not m:
             continue
-        per[cls] = dict(kernel=k, fetch_bytes=fe[k][0] * 1024 * ff, write_bytes=wr[k][0] * 1024 * wf,
-                        bytes=fe[k][0] * 1024 * ff + wr[k][0] * 1024 * wf, dispatches=fe[k][1],
+        per[cls] = dict(kernel=" + ".join(counted), fetch_bytes=fb, write_bytes=wb, bytes=fb + wb, dispatches=n,
                         sources=kernel_sources_hash(SOURCES_OF_CLASS[cls]))
     rec = {
            "workload": DEFAULT_WORKLOAD,
