@@ -310,8 +310,8 @@ static void free_ws(sd_engine e)
 // rows; one prompt of 2500 in 4.5 ms, in steps' 320 rows 14.1).
 constexpr int PREFILL_ROWS = 2560;
 
-// The workspace for a prefill of `rows` rows in all.  One of PREFILL_ROWS (546 MB
-// at the 32B shape, 342 at the 8B shape) is taken by the first prefill that does
+// The workspace for a prefill of `rows` rows in all.  One of PREFILL_ROWS (550 MB
+// at the 32B shape, 344 at the 8B shape) is taken by the first prefill that does
 // not fit a step's rows, since the KV cache is there by then and an engine that
 // never prefills needs none; only where it is at most a quarter of the free
 // memory, and not while the stream is being captured.  The thread's capture mode
