@@ -193,9 +193,9 @@ def test_dense_gemm_verify_rows(M):
 @pytest.mark.parametrize("M", [1, 5, 16, 33, 64])
 def test_dense_gemm_decode_rows(M, N):
     """The bf16 GEMM at the AR step's and draft LM head's row counts (M <= 64):
-    the DMA-fed 64-row tiles where N is a multiple of 256 (rows past M repeat
-    the last row and are never stored), the register-streaming kernel
-    otherwise (N = 4224), against torch in fp32 on the same bf16 inputs."""
+    the DMA-fed 64-row tiles (rows past M repeat the last row and are never
+    stored), N a multiple of 256 and an odd one of 128 (4224), against torch in
+    fp32 on the same bf16 inputs."""
     say("decode-rows gemm", M, N)
     g = torch.Generator(device="cuda").manual_seed(1000 + M)
     K = 1024
